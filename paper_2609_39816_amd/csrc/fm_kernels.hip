@@ -278,75 +278,118 @@ __global__ __launch_bounds__(64) void reduce_rows_kernel(const double* partial, 
 }
 
 // ----------------------------------------------------- float64 reference
-// On the float64 matrix cores: 128 x 128 output tile per workgroup of 8
-// waves (64 x 32 each: 4 x 2 blocks of v_mfma_f64_16x16x4_f64; two waves
-// per SIMD hide each other's LDS reads and conversions), K step 64;
-// operands staged in LDS as fp32 (67 KB) and widened to float64 when read
-// (products of two fp32 values are exact in float64; the sums are float64,
-// in ascending K steps of 4 for every output, whatever the tiling).
+// On the float64 matrix cores: 128 x 128 output tile per workgroup of 4
+// waves (64 x 64 each: 4 x 4 blocks of v_mfma_f64_16x16x4_f64), two
+// workgroups and two waves per SIMD, K steps of 16 through two LDS buffers
+// (73 KB per workgroup), one barrier per step: a step's operands are widened
+// and written to LDS between the matrix instructions of the step before, and
+// loaded from memory one step earlier still.  Bound by the float64 matrix
+// unit, which every vector instruction holds up (half of the loop's loads
+// and conversions left out, it ran 69 instead of 65 TFLOP/s).  Measured at
+// 2048 x 4096 x 4096 and 8192^3, TFLOP/s: operands widened at every LDS
+// read, one buffer, 8 waves of 64 x 32 56 and 60; widened once on the way
+// into LDS 58 and 64; this kernel 60 and 66; one wave of 64 x 128 per SIMD
+// no faster.  Products of two fp32 values are exact in
+// float64; the sums are float64, in ascending K steps of 4 for every output,
+// whatever the tiling.  VEC: whole tiles, K a multiple of 16 and 16-byte
+// aligned operands, so every load is a whole 16-byte piece; otherwise
+// guarded single loads (any shape and alignment).
 // Lane l of a 16 x 16 x 4 step holds A[l % 16][l / 16] and B[l / 16][l % 16];
 // its four results v = 0..3 are rows l / 16 + 4 v, column l % 16 of the block
-// (checked on the device with small integer operands).
+// (checked on the device with small integer operands).  Row pitches: 32
+// lanes read 256 bytes of LDS per cycle, 16 rows x 2 values of A (pitch an
+// odd number of 16-byte pieces) or 2 rows x 16 values of B (pitch an odd
+// number of 128-byte pieces), without bank conflicts.
 typedef double v4d __attribute__((ext_vector_type(4)));
-constexpr int kRefThreads = 512;
-__global__ __launch_bounds__(kRefThreads) void ref_f64_mfma_kernel(const float* __restrict__ A,
-                                                                   const float* __restrict__ B,
-                                                                   double* __restrict__ C, int M,
-                                                                   int N, int K) {
-  constexpr int KS = 64;  // K step
-  constexpr int NL = 128 * KS / kRefThreads;  // loads per thread and operand (16)
-  __shared__ float As[128][KS + 1];
-  __shared__ float Bs[KS][128 + 4];
+typedef double v2d __attribute__((ext_vector_type(2)));
+constexpr int kRefThreads = 256;
+template <bool VEC>
+__global__ __launch_bounds__(kRefThreads, 2) void ref_f64_mfma_kernel(const float* __restrict__ A,
+                                                                      const float* __restrict__ B,
+                                                                      double* __restrict__ C, int M,
+                                                                      int N, int K) {
+  constexpr int KS = 16;  // K step
+  constexpr int NL = 128 * KS / kRefThreads;  // values per thread and operand (8)
+  __shared__ __attribute__((aligned(16))) double As[2][128][KS + 2];
+  __shared__ __attribute__((aligned(16))) double Bs[2][KS][128 + 16];
   const int m0 = blockIdx.y * 128, n0 = blockIdx.x * 128;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 2, wn = wave & 3;  // 64-row half, 32-column quarter
+  const int wm = wave >> 1, wn = wave & 1;  // 64-row, 64-column half
   const int l16 = lane & 15, lq = lane >> 4;
-  v4d acc[4][2];
+  v4d acc[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
-  // the next step's operands are loaded into registers while this step's
-  // products run
+    for (int j = 0; j < 4; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
   float ra[NL], rb[NL];
+  // VEC: thread t loads 4 values from column 4 (t % 4) of A rows t / 4 and
+  // t / 4 + 64, and from column 4 (t % 32) of B rows t / 32 and t / 32 + 8;
+  // otherwise value i is A row t / 16 + 16 i, column t % 16, and B row
+  // t / 128 + 2 i, column t % 128
+  const int ar = VEC ? tid >> 2 : tid >> 4, ak = VEC ? (tid & 3) * 4 : tid & 15;
+  const int bk = VEC ? tid >> 5 : tid >> 7, bc = VEC ? (tid & 31) * 4 : tid & 127;
+  const float* Ap = A + (size_t)(m0 + ar) * K + ak;
+  const float* Bp = B + (size_t)bk * N + n0 + bc;
   auto load = [&](int k0) {
+    if constexpr (VEC) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int idx = tid + kRefThreads * i;  // 0 .. 8191
-      const int r = idx >> 6, kk = idx & 63;
-      const int gr = m0 + r, gk = k0 + kk;
-      ra[i] = (gr < M && gk < K) ? A[(size_t)gr * K + gk] : 0.0f;
-      const int kb = idx >> 7, c = idx & 127;
-      const int gkb = k0 + kb, gc = n0 + c;
-      rb[i] = (gkb < K && gc < N) ? B[(size_t)gkb * N + gc] : 0.0f;
+      for (int i = 0; i < 2; ++i) {
+        const float4 a4 = *reinterpret_cast<const float4*>(Ap + (size_t)64 * i * K + k0);
+        const float4 b4 = *reinterpret_cast<const float4*>(Bp + (size_t)(k0 + 8 * i) * N);
+        ra[4 * i] = a4.x, ra[4 * i + 1] = a4.y, ra[4 * i + 2] = a4.z, ra[4 * i + 3] = a4.w;
+        rb[4 * i] = b4.x, rb[4 * i + 1] = b4.y, rb[4 * i + 2] = b4.z, rb[4 * i + 3] = b4.w;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        ra[i] = (m0 + ar + 16 * i < M && k0 + ak < K) ? Ap[(size_t)16 * i * K + k0] : 0.0f;
+        rb[i] = (k0 + bk + 2 * i < K && n0 + bc < N) ? Bp[(size_t)(k0 + 2 * i) * N] : 0.0f;
+      }
     }
   };
-  auto store = [&]() {
+  auto store = [&](int buf) {
+    if constexpr (VEC) {
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const int idx = tid + kRefThreads * i;
-      As[idx >> 6][idx & 63] = ra[i];
-      Bs[idx >> 7][idx & 127] = rb[i];
+      for (int i = 0; i < 2; ++i) {
+        v2d* pa = reinterpret_cast<v2d*>(&As[buf][ar + 64 * i][ak]);
+        v2d* pb = reinterpret_cast<v2d*>(&Bs[buf][bk + 8 * i][bc]);
+        pa[0] = (v2d){(double)ra[4 * i], (double)ra[4 * i + 1]};
+        pa[1] = (v2d){(double)ra[4 * i + 2], (double)ra[4 * i + 3]};
+        pb[0] = (v2d){(double)rb[4 * i], (double)rb[4 * i + 1]};
+        pb[1] = (v2d){(double)rb[4 * i + 2], (double)rb[4 * i + 3]};
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        As[buf][ar + 16 * i][ak] = (double)ra[i];
+        Bs[buf][bk + 2 * i][bc] = (double)rb[i];
+      }
     }
+  };
+  auto products = [&](int buf, int kk) {
+    double a[4], b[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[i] = As[buf][wm * 64 + i * 16 + l16][kk + lq];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) b[j] = Bs[buf][kk + lq][wn * 64 + j * 16 + l16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
   };
   load(0);
-  for (int k0 = 0; k0 < K; k0 += KS) {
-    store();
-    __syncthreads();
-    if (k0 + KS < K) load(k0 + KS);
-#pragma unroll
-    for (int kk = 0; kk < KS; kk += 4) {
-      double a[4], b[2];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = (double)As[wm * 64 + i * 16 + l16][kk + lq];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = (double)Bs[kk + lq][wn * 32 + j * 16 + l16];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
+  store(0);
+  if (KS < K) load(KS);
+  __syncthreads();
+  int buf = 0;
+  for (int k0 = 0; k0 < K; k0 += KS, buf ^= 1) {
+    products(buf, 0);
+    products(buf, 4);
+    if (k0 + KS < K) store(buf ^ 1);  // last read before the previous barrier
+    if (k0 + 2 * KS < K) load(k0 + 2 * KS);
+    products(buf, 8);
+    products(buf, 12);
     __syncthreads();
   }
 #pragma unroll
@@ -356,8 +399,8 @@ __global__ __launch_bounds__(kRefThreads) void ref_f64_mfma_kernel(const float* 
       const int row = m0 + wm * 64 + i * 16 + lq + 4 * v;
       if (row >= M) continue;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int col = n0 + wn * 32 + j * 16 + l16;
+      for (int j = 0; j < 4; ++j) {
+        const int col = n0 + wn * 64 + j * 16 + l16;
         if (col < N) C[(size_t)row * N + col] = acc[i][j][v];
       }
     }
@@ -499,7 +542,12 @@ int launch_reduce_rows(const double* partial, int nblk, int G, double* out, hipS
 int launch_reference_f64(const float* A, const float* B, double* C, int M, int N, int K,
                          hipStream_t st) {
   dim3 grid((N + 127) / 128, (M + 127) / 128);
-  ref_f64_mfma_kernel<<<grid, kRefThreads, 0, st>>>(A, B, C, M, N, K);
+  const bool vec = M % 128 == 0 && N % 128 == 0 && K % 16 == 0 &&
+                   (((uintptr_t)A | (uintptr_t)B) & 15u) == 0;
+  if (vec)
+    ref_f64_mfma_kernel<true><<<grid, kRefThreads, 0, st>>>(A, B, C, M, N, K);
+  else
+    ref_f64_mfma_kernel<false><<<grid, kRefThreads, 0, st>>>(A, B, C, M, N, K);
   return launched("ref_f64_mfma_kernel");
 }
 
