@@ -125,6 +125,34 @@ int chunk_pattern(const Tables& T, int side, int g0, int n) {
   return p;
 }
 
+// Consecutive gauges of a chunk that one family kernel takes: gauges
+// [g0 + at, g0 + at + n) share the pattern (and, on A's and B's sides, whether
+// they are sign variants of the family's base scheme).
+struct Run {
+  int at, n, pattern;
+};
+
+// The runs of [g0, g0 + n) on one side (A 0, B 1, W 2).  An orbit under dense
+// gauges usually starts with the identity, whose sparse lists belong to
+// another family; as one chunk both would go to the generic kernels (measured
+// on 31 dense gauges and the identity of Laderman, 3072 x 4608 x 12288: 5.4 ms
+// per formation pass and 15.5 ms for the reconstruction, against 0.3-1.8 ms
+// and 2.6 ms by family).  A launch per run pays while runs average at least
+// 8 gauges; with shorter ones (no known use) the chunk stays whole.
+std::vector<Run> family_runs(const Tables& T, int side, int g0, int n) {
+  std::vector<Run> runs;
+  for (int g = g0; g < g0 + n; ++g) {
+    const bool same = g > g0 && T.pat[side][g] == T.pat[side][g - 1] &&
+                      (side == 2 || T.trie[side][g] == T.trie[side][g - 1]);
+    if (same)
+      runs.back().n += 1;
+    else
+      runs.push_back({g - g0, 1, T.pat[side][g]});
+  }
+  if ((int)runs.size() > 1 + n / 8) runs.assign(1, Run{0, n, chunk_pattern(T, side, g0, n)});
+  return runs;
+}
+
 // Workspace layout for G gauges processed `chunk` at a time.
 struct Layout {
   // *2: a second set of a chunk's maxima, scales and block products when the
@@ -486,6 +514,23 @@ void set_trie(FormArgs& f, const Tables& T, char* ws, const Layout& L, int side,
   f.sgn = f.trie ? (const uint64_t*)(ws + L.sg[side]) + g0 : nullptr;
 }
 
+// One formation pass (mode 0 maxima, 1 codes) of the gauges [g0, g0 + a.G) of
+// one side, a launch per run of one family; span: scales per block-sum tensor.
+int launch_form_runs(const FormArgs& a, int mode, int side, const Tables& T, char* ws,
+                     const Layout& L, int g0, size_t span, hipStream_t st) {
+  for (const Run& r : family_runs(T, side, g0, a.G)) {
+    FormArgs f = a;
+    f.G = r.n;
+    f.off += (size_t)r.at * (a.R + 1);
+    f.amax += (size_t)r.at * a.R * span;
+    f.q += (size_t)r.at * a.R * span;
+    f.codes += (size_t)r.at * a.R * a.br * a.bc;
+    set_trie(f, T, ws, L, side, g0 + r.at, r.n);
+    if (int rc = launch_form(f, mode, r.pattern, side, st)) return rc;
+  }
+  return FM_OK;
+}
+
 // Formation arguments of both sides of the gauges [g0, g0 + n) with one
 // scale per block-sum tensor, maxima and scales in the first set of L.
 void tensor_form_args(const Geometry& geo, const float* A, const float* Bt, char* ws,
@@ -532,12 +577,12 @@ int form_codes_and_next_maxima(const Geometry& geo, const float* A, const float*
     const bool merge = n1 > 0 && pq >= 0 && pq == pm;
     int rc = merge ? launch_form_merged(aq, am, pq, side, st) : 1;
     const bool merged = merge && rc != 1;
-    if (!merged) rc = launch_form(aq, 1, pq, side, st);
+    if (!merged) rc = launch_form_runs(aq, 1, side, T, ws, L, g0, 1, st);
     if (rc) return rc;
     timing_end(T_FORM_QUANT, st);
     if (n1 > 0 && !merged) {
       timing_begin(T_FORM_AMAX, st);
-      if ((rc = launch_form(am, 0, pm, side, st))) return rc;
+      if ((rc = launch_form_runs(am, 0, side, T, ws, L, g0 + n, 1, st))) return rc;
       timing_end(T_FORM_AMAX, st);
     }
   }
@@ -565,7 +610,8 @@ int form_chunk(const Geometry& geo, const float* A, const float* Bt, char* ws, c
   auto off = [&](int k) { return (const int32_t*)(ws + L.off[k]) + (size_t)g0 * (R + 1); };
   auto idx = [&](int k) { return (const int32_t*)(ws + L.idx[k]); };
   auto coef = [&](int k) { return (const float*)(ws + L.coef[k]); };
-  const int pa = chunk_pattern(T, 0, g0, n), pb = chunk_pattern(T, 1, g0, n);
+  const int pb = chunk_pattern(T, 1, g0, n);
+  const size_t spans[2] = {(size_t)scales_a(geo, scale_mode), (size_t)scales_b(geo, scale_mode)};
   FormArgs fa{A,    geo.M, geo.K, geo.gm, geo.gk, geo.Mb, geo.Kb, off(0), idx(0), coef(0), R, n,
               amax, q,     Tq,    fmt,    per_row, mode == FM_SCALE_GROUP ? 2 : 1};
   FormArgs fb{Bt, geo.N, geo.K, geo.gn, geo.gk, geo.Nb, geo.Kb, off(1), idx(1), coef(1), R, n,
@@ -575,7 +621,7 @@ int form_chunk(const Geometry& geo, const float* A, const float* Bt, char* ws, c
   if (int rc = launch_fill_u32(amax, na + nb, 0u, st)) return rc;
   for (int side = 0; side < 2; ++side) {
     timing_begin(T_FORM_AMAX, st);
-    if (int rc = launch_form(side ? fb : fa, 0, side ? pb : pa, side, st)) return rc;
+    if (int rc = launch_form_runs(side ? fb : fa, 0, side, T, ws, L, g0, spans[side], st)) return rc;
     timing_end(T_FORM_AMAX, st);
   }
   if (int rc = launch_scales(amax, q, dd, (int)(na + nb), fmt, (uint32_t*)(ws + L.flags), st))
@@ -584,7 +630,7 @@ int form_chunk(const Geometry& geo, const float* A, const float* Bt, char* ws, c
   const int quant_sides = repair_weights(scale_mode) ? 1 : 2;
   for (int side = 0; side < quant_sides; ++side) {
     timing_begin(T_FORM_QUANT, st);
-    if (int rc = launch_form(side ? fb : fa, 1, side ? pb : pa, side, st)) return rc;
+    if (int rc = launch_form_runs(side ? fb : fa, 1, side, T, ws, L, g0, spans[side], st)) return rc;
     timing_end(T_FORM_QUANT, st);
   }
   if (repair_weights(scale_mode)) {
@@ -1411,12 +1457,10 @@ int fm_orbit_eval_scaled(const fm_scheme* const* gauged, int G, const float* A, 
     const int n0 = std::min(chunk, G);
     FormArgs fa, fb;
     tensor_form_args(geo, Aform, Bt, ws, L, 0, n0, fmt, Tq, Sq, fa, fb);
-    set_trie(fa, T, ws, L, 0, 0, n0);
-    set_trie(fb, T, ws, L, 1, 0, n0);
     if ((rc = launch_fill_u32(fa.amax, (size_t)2 * n0 * geo.R, 0u, st))) return rc;
     for (int side = 0; side < 2; ++side) {
       timing_begin(T_FORM_AMAX, st);
-      if ((rc = launch_form(side ? fb : fa, 0, chunk_pattern(T, side, 0, n0), side, st))) return rc;
+      if ((rc = launch_form_runs(side ? fb : fa, 0, side, T, ws, L, 0, 1, st))) return rc;
       timing_end(T_FORM_AMAX, st);
     }
     if ((rc = launch_scales(fa.amax, (float*)(ws + L.q), (float*)(ws + L.d), 2 * n0 * geo.R, fmt,
@@ -1446,9 +1490,11 @@ int fm_orbit_eval_scaled(const fm_scheme* const* gauged, int G, const float* A, 
     if (c >= 1 && (rc = pipe.wait_reconstructed(buf ^ 1))) return rc;
     // products of whole tiles go to the reconstruction in the tiled layout
     // (contiguous stores) when a family kernel reconstructs them
-    const int rpat = chunk_pattern(T, 2, g0, n);
+    const std::vector<Run> rruns = family_runs(T, 2, g0, n);
+    bool rfam = true;
+    for (const Run& r : rruns) rfam = rfam && r.pattern >= 0;
     const int trows = block_gemm_tile_rows(geo.Mb, geo.Nb, geo.Kb, base_mode(scale_mode), bf);
-    const bool tiled = scale_mode == FM_SCALE_TENSOR && rpat >= 0 && trows > 0 &&
+    const bool tiled = scale_mode == FM_SCALE_TENSOR && rfam && trows > 0 &&
                        geo.Mb % trows == 0 && geo.Nb % 128 == 0 && geo.N % 4 == 0 &&
                        geo.gm * geo.gn <= 64 && (size_t)geo.R * geo.Mb * geo.Nb * 4 < ((size_t)1 << 32);
     timing_begin(T_BLOCK_GEMM, st);
@@ -1465,7 +1511,15 @@ int fm_orbit_eval_scaled(const fm_scheme* const* gauged, int G, const float* A, 
     ra.tiled = tiled ? trows : 0;
     const int nblk = recon_blocks(ra);
     timing_begin(T_RECON, rs);
-    if ((rc = launch_recon(ra, rpat, rs))) return rc;
+    for (const Run& r : rruns) {
+      ReconArgs rr = ra;
+      rr.G = r.n;
+      rr.off += (size_t)r.at * (geo.R + 1);
+      rr.Mprod = (const float*)((const char*)ra.Mprod +
+                                (size_t)r.at * geo.R * geo.Mb * geo.Nb * (bf ? 2 : 4));
+      rr.partial += (size_t)r.at * nblk;
+      if ((rc = launch_recon(rr, r.pattern, rs))) return rc;
+    }
     timing_end(T_RECON, rs);
     if ((rc = launch_reduce_rows((double*)(ws + L.partial), nblk, n, errsq + g0, rs))) return rc;
     if (pipe.on && (rc = pipe.reconstructed(buf))) return rc;
