@@ -555,19 +555,26 @@ __global__ __launch_bounds__(DNT) void gemm_dma_kernel(const uint8_t* __restrict
 }
 
 
-// Wide persistent kernel (tensor or row/column scales, bf16 products, Mb a
-// multiple of 512, Nb of 128, Kb of 64): workgroup tile 512 x 128, K step 64
-// bytes, a ring of 4 LDS stages of 40 KB (512 + 128 rows of 64 bytes; all
-// 160 KB of the CU's LDS) filled by direct global-to-LDS loads two to three
-// K steps ahead, 8 waves, two per SIMD.  Each wave computes 128 rows x 64
-// columns = 4 x 2 tiles of 32 x 32 (v_mfma_f32_32x32x16_bf16, 128
-// accumulators), so a widened A fragment feeds 2 matrix instructions and a
-// B fragment 4, and the two waves of a SIMD share its matrix unit: while one
-// issues its loads, LDS reads or conversions (which stall a wave, and with
-// one wave per SIMD the matrix unit with it), the other's matrix
-// instructions run.  Waves w and w + 4 (one SIMD) take the same 128 A rows
-// (w % 4) and the two 64-column halves of B.  Per stage a wave loads 4 x 16
-// A rows and 16 B rows (5 of the 40 wave-loads).  The raw codes of a stage
+// Wide persistent kernel (tensor or row/column scales, bf16 products, Kb a
+// multiple of 64): workgroup tile 256 x 256 (WN = 4) or 512 x 128 (WN = 2), K
+// step 64 bytes, a ring of 4 LDS stages (512 or 640 rows of 64 bytes: 32 or
+// 40 KB) filled by direct global-to-LDS loads two to three K steps ahead, 8
+// waves, two per SIMD.  Each wave computes 128 rows x 64 columns = 4 x 2
+// tiles of 32 x 32 (v_mfma_f32_32x32x16_bf16, 128 accumulators), so a widened
+// A fragment feeds 2 matrix instructions and a B fragment 4, and the two
+// waves of a SIMD share its matrix unit: while one issues its loads, LDS
+// reads or conversions (which stall a wave, and with one wave per SIMD the
+// matrix unit with it), the other's matrix instructions run.  Wave w takes
+// the 128 A rows w % (8 / WN) and the 64 columns w / (8 / WN).
+//
+// Bound by the matrix cores at the clock they hold and by the operand loads
+// from L2 (about 19 bytes per cycle and CU when loading alone): the square
+// tile loads 512 rows per K step for the 65536 outputs the other loads 640
+// for, and where both fit it was the faster: 49 x 32 products of 512 x 1024 x
+// 1024 in 1.46 against 1.55 ms, 23 x 32 of 1024 x 1536 x 4096 in 8.05 against
+// 8.5 ms.  The 512 x 128 tile serves column counts that are whole 128s only.
+// Per stage a wave loads its share of the A and B rows (4 or 5 wave-loads of
+// 1 KB).  The raw codes of a stage
 // are read from LDS in two halves (the first 16 bytes of each lane's 32,
 // sub-steps 0 and 1; then the second), each as soon as the previous stage's
 // half is widened, so one stage of raw codes and two sub-steps of widened
@@ -582,7 +589,7 @@ __global__ __launch_bounds__(DNT) void gemm_dma_kernel(const uint8_t* __restrict
 // served per LDS cycle of a 16-byte fragment read (16 consecutive rows, 4
 // rows per 256-byte bank window) then hit 16 distinct 16-byte bank groups.
 namespace wide {
-constexpr int BM = 512, BN = 128, KS = 64;
+constexpr int KS = 64;
 
 // global_load_lds_dwordx4 with a scalar base and a 32-bit per-lane offset:
 // lane L writes the 16 bytes it fetched at M0 + 16 L (M0 written by SALU
@@ -600,33 +607,47 @@ __device__ __forceinline__ void dma16s(const void* sbase, uint32_t voff, uint32_
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 namespace wide8 {
-constexpr int BM = 512, BN = 128, KS = 64, NT = 512, NSTG = 4;
-constexpr int ROWS = BM + BN;         // rows of KS bytes per stage
-constexpr int STAGE = ROWS * KS;      // 40 KB
-constexpr int LOADS = ROWS / 16 / 8;  // 1 KB wave-loads per wave per stage (5)
-constexpr int STORES = 32;            // 16-byte stores per lane per tile
+constexpr int KS = 64, NT = 512, NSTG = 4;
+constexpr int STORES = 32;  // 16-byte stores per lane per tile
+
+// WN waves side by side: 2 for 512 x 128 tiles, 4 for 256 x 256
+template <int WN>
+struct Tile {
+  static constexpr int BM = 8 / WN * 128, BN = WN * 64;
+  static constexpr int ROWS = BM + BN;         // rows of KS bytes per stage
+  static constexpr int STAGE = ROWS * KS;      // 40 KB or 32 KB
+  static constexpr int LA = BM / 16 / 8;       // 1 KB wave-loads per wave per stage of A
+  static constexpr int LOADS = ROWS / 16 / 8;  // and of both operands (5 or 4)
+  // loads of the stage three ahead issued in the first of an iteration's four
+  // phases; the others issue one each
+  static constexpr int L0 = LOADS - 3;
+};
 
 // the counts used: after a tile's stores, or not; anything less waits for
 // everything (a count above the one needed waits for more than needed)
+template <int WN>
 __device__ __forceinline__ void wait_vm(int n) {
-  if (n >= LOADS + 2 + STORES) ring::wait_vm_n<LOADS + 2 + STORES>();
-  else if (n >= LOADS + 2) ring::wait_vm_n<LOADS + 2>();
+  constexpr int N1 = Tile<WN>::LOADS + Tile<WN>::L0;
+  if (n >= N1 + STORES) ring::wait_vm_n<N1 + STORES>();
+  else if (n >= N1) ring::wait_vm_n<N1>();
   else ring::wait_vm_n<0>();
 }
 }  // namespace wide8
 
-template <int FMT, int SC>
+template <int FMT, int SC, int WN>
 __global__ __launch_bounds__(wide8::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict__ Sq,
                        const float* __restrict__ dT, const float* __restrict__ dS,
                        float* __restrict__ Mout, int Mb, int Nb, int Kb, int tiles_m, int tiles_n,
                        int total, int tiled) {
   using namespace wide8;
+  using TL = Tile<WN>;
+  constexpr int BM = TL::BM, BN = TL::BN, STAGE = TL::STAGE, LOADS = TL::LOADS, LA = TL::LA;
   __shared__ __attribute__((aligned(1024))) uint8_t lds[NSTG * STAGE];
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave & 3, wn = wave >> 2;
+  const int wm = wave % (8 / WN), wn = wave / (8 / WN);
   const int r32 = lane & 31, h = lane >> 5;
   const int tiles = tiles_m * tiles_n;
   const int nk = Kb / KS;
@@ -651,20 +672,21 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
   const uint32_t dma_off =
       (uint32_t)(lane >> 2) * (uint32_t)Kb + (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
   const size_t kb16 = (size_t)16 * Kb;
-  // this wave's first A row (64 wave) and B row (16 wave) of a tile's panels
+  // this wave's first A row (16 LA wave) and B row of a tile's panels
   auto tile_base = [&](int tile, const uint8_t*& Ab, const uint8_t*& Bb) {
     const int b = tile / tiles, tt = tile - b * tiles;
     const int tmi = tt / tiles_n;
-    Ab = Tq + ((size_t)b * Mb + (size_t)tmi * BM + (size_t)wave * 64) * Kb;
-    Bb = Sq + ((size_t)b * Nb + (size_t)(tt - tmi * tiles_n) * BN + (size_t)wave * 16) * Kb;
+    Ab = Tq + ((size_t)b * Mb + (size_t)tmi * BM + (size_t)wave * (16 * LA)) * Kb;
+    Bb = Sq + ((size_t)b * Nb + (size_t)(tt - tmi * tiles_n) * BN + (size_t)wave * (16 * (LOADS - LA))) * Kb;
   };
-  // wave-load j of a stage: j < 4 A rows 64 wave + 16 j, j = 4 B rows 16 wave
+  // wave-load j of a stage: j < LA 16 A rows, otherwise 16 B rows
   auto dma_one = [&](const uint8_t* Ab, const uint8_t* Bb, int kt, int buf, int j) {
     const uint32_t l0 = lds_base + (uint32_t)(buf * STAGE);
-    if (j < 4)
-      wide::dma16s(Ab + j * kb16 + kt * KS, dma_off, l0 + (uint32_t)((wave * 64 + 16 * j) * KS));
+    if (j < LA)
+      wide::dma16s(Ab + j * kb16 + kt * KS, dma_off, l0 + (uint32_t)((wave * LA + j) * 16 * KS));
     else
-      wide::dma16s(Bb + kt * KS, dma_off, l0 + (uint32_t)((BM + wave * 16) * KS));
+      wide::dma16s(Bb + (j - LA) * kb16 + kt * KS, dma_off,
+                   l0 + (uint32_t)((BM + (wave * (LOADS - LA) + j - LA) * 16) * KS));
   };
   auto issue = [&](const uint8_t* Ab, const uint8_t* Bb, int kt, int buf) {
 #pragma unroll
@@ -716,9 +738,11 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
     const int m0 = tmi * BM, n0 = (tt - tmi * tiles_n) * BN;
     float* Mo = Mout + (size_t)b * Mb * Nb;
     const int r_base = m0 + wm * 128 + r32, c_base = n0 + wn * 64 + 4 * h;
-    // tiled layout: pieces in the order (row block wm, i, column tile 2 wn +
-    // j, column group g, lane), one contiguous kilobyte per wave store
-    float* tbase = Mo + (size_t)tt * (BM * BN) + (size_t)wm * (128 * 128) + lane * 4;
+    // tiled layout: the 128 x 128 piece this wave has half of, its values in
+    // the order (i, column tile of 32, column group g, lane), one contiguous
+    // kilobyte per wave store
+    const int pr = tmi * (BM / 128) + wm, pc = n0 / 128 + (wn >> 1);
+    float* tbase = Mo + ((size_t)pr * (Nb / 128) + pc) * (128 * 128) + lane * 4;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = r_base + i * 32;
@@ -742,7 +766,7 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
           o[3] = (acc[i][j][4 * g + 3] * sT) * sS.w;
           if (tiled)
             __builtin_nontemporal_store(
-                o, reinterpret_cast<v4f*>(tbase + ((i * 4 + 2 * wn + j) * 4 + g) * 256));
+                o, reinterpret_cast<v4f*>(tbase + ((i * 4 + 2 * (wn & 1) + j) * 4 + g) * 256));
           else
             *reinterpret_cast<v4f*>(prow + j * 32 + 8 * g) = o;
         }
@@ -751,9 +775,9 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
   };
 
   // Iteration s over the (tile, K step) pairs p_s, in four phases of 8
-  // matrix instructions (one sub-step each), with the 5 wave-loads of
+  // matrix instructions (one sub-step each), with the wave-loads of
   // p_{s+3} (into the buffer of p_{s-1}) after matrix instructions 1 and 5:
-  //   A: sub-step 0 (slot 0), widening sub-step 1 into slot 1; 2 loads;
+  //   A: sub-step 0 (slot 0), widening sub-step 1 into slot 1; 1 or 2 loads;
   //   wait until p_{s+1} has landed and every wave's reads of p_s are done;
   //   B: sub-step 1 (slot 1), widening sub-step 2 into slot 0, reading the
   //      first half of p_{s+1}; 1 load;
@@ -788,10 +812,10 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
   };
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
-  using I4 = std::integral_constant<int, 4>;
-  using I5 = std::integral_constant<int, 5>;
+  using J1 = std::integral_constant<int, TL::L0>;
+  using J2 = std::integral_constant<int, TL::L0 + 1>;
+  using J3 = std::integral_constant<int, TL::L0 + 2>;
+  using J4 = std::integral_constant<int, LOADS>;
   int t1 = t, k1 = 0;  // p_{s+1}
   advance(t1, k1);
   int t2 = t1, k2 = k1;  // p_{s+2}
@@ -813,7 +837,7 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
   }
   const uint8_t *A3 = A0, *B3 = B0;  // panels of the tile of p_{s+3}
   if (t3 < t_end && t3 != t2) tile_base(t3, A3, B3);
-  wait_vm(t1 < t_end ? after1 + LOADS : 0);  // p_0 has landed
+  wait_vm<WN>(t1 < t_end ? after1 + LOADS : 0);  // p_0 has landed
   FM_COMPILER_FENCE();
   __builtin_amdgcn_s_barrier();
   FM_COMPILER_FENCE();
@@ -832,13 +856,13 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
     for (int kk = 0; kk < nk; ++kk) {
       const int b3 = cb == 0 ? NSTG - 1 : cb - 1;  // buffer of p_{s+3} (that of p_{s-1})
       // A
-      mma_dma(0, A3, B3, k3, b3, I0{}, I2{});
+      mma_dma(0, A3, B3, k3, b3, I0{}, J1{});
       widen_sub(1, 1);
       groups(std::integral_constant<int, 3>{}, I0{});
       pin(1);
       __builtin_amdgcn_sched_barrier(0);
-      // p_{s+1} was issued before p_{s+2}'s 5 loads and 2 of p_{s+3}
-      wait_vm(after1 + 2);
+      // p_{s+1} was issued before p_{s+2}'s loads and the first of p_{s+3}
+      wait_vm<WN>(after1 + TL::L0);
       __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's reads of p_s are done
       FM_COMPILER_FENCE();
       __builtin_amdgcn_s_barrier();
@@ -846,20 +870,20 @@ void gemm_wide8_kernel(const uint8_t* __restrict__ Tq, const uint8_t* __restrict
       const int nb = cb == NSTG - 1 ? 0 : cb + 1;
       more = t1 < t_end;
       // B
-      mma_dma(1, A3, B3, k3, b3, I2{}, I3{});
+      mma_dma(1, A3, B3, k3, b3, J1{}, J2{});
       widen_sub(2, 0);
       read_half(nb, C0{});
       groups(std::integral_constant<int, 3>{}, I1{});
       pin(0);
       __builtin_amdgcn_sched_barrier(0);
       // C
-      mma_dma(0, A3, B3, k3, b3, I3{}, I4{});
+      mma_dma(0, A3, B3, k3, b3, J2{}, J3{});
       widen_sub(3, 1);
       groups(std::integral_constant<int, 3>{}, I0{});
       pin(1);
       __builtin_amdgcn_sched_barrier(0);
       // D
-      mma_dma(1, A3, B3, k3, b3, I4{}, I5{});
+      mma_dma(1, A3, B3, k3, b3, J3{}, J4{});
       read_half(nb, C1{});
       widen_sub(0, 0);
       groups(std::integral_constant<int, 3>{}, I1{});
@@ -895,15 +919,21 @@ bool wide_enabled() {
   return on;
 }
 
-bool use_wide(int Mb, int Nb, int Kb, int sc, bool out_bf16) {
-  return wide_enabled() && g_block_product_arith == FM_ACC_BF16 && (sc == 0 || sc == 1) &&
-         !out_bf16 && Mb % wide::BM == 0 && Nb % wide::BN == 0 && Kb % wide::KS == 0;
+// Waves side by side of the wide kernel's tile for these arguments: 4 (256 x
+// 256), 2 (512 x 128), or 0 when the products are no whole tiles of either.
+int wide_waves(int Mb, int Nb, int Kb, int sc, bool out_bf16) {
+  if (!wide_enabled() || g_block_product_arith != FM_ACC_BF16 || (sc != 0 && sc != 1) ||
+      out_bf16 || Kb % wide8::KS)
+    return 0;
+  if (Mb % 256 == 0 && Nb % 256 == 0) return 4;
+  if (Mb % 512 == 0 && Nb % 128 == 0) return 2;
+  return 0;
 }
 }  // namespace
 
 int block_gemm_tile_rows(int Mb, int Nb, int Kb, int scale_mode, bool out_bf16) {
   const int sc = scale_mode == FM_SCALE_ROWCOL ? 1 : (scale_mode == FM_SCALE_GROUP ? 2 : 0);
-  if (use_wide(Mb, Nb, Kb, sc, out_bf16)) return wide::BM;
+  if (wide_waves(Mb, Nb, Kb, sc, out_bf16)) return 128;
   if (Kb % GK == 0) return DBM;
   return 0;
 }
@@ -920,20 +950,27 @@ int launch_block_gemm_sc(const uint8_t* Tq, const uint8_t* Sq, const float* dT, 
                          float* Mout, int batch, int Mb, int Nb, int Kb, int fmt, hipStream_t st,
                          int tiled = 0) {
   const bool fp8acc = g_block_product_arith == FM_ACC_FP8;
-  if (use_wide(Mb, Nb, Kb, SC, OB)) {
+  if (const int wn = wide_waves(Mb, Nb, Kb, SC, OB)) {
     if constexpr (SC == 0 || SC == 1) {
-      // persistent: one 160 KB-LDS workgroup of 4 waves per CU
-      const int tm = Mb / wide::BM, tn = Nb / wide::BN;
+      // persistent: one workgroup of 8 waves (160 or 128 KB of LDS) per CU
+      const int tm = Mb / (8 / wn * 128), tn = Nb / (wn * 64);
       const long long total = (long long)batch * tm * tn;
       if (total > 0x7fffffffLL) return fail(FM_E_SHAPE, "too many GEMM tiles in one launch");
       const int T = (int)total;
       const int grid = (int)std::min<long long>(total, 256);
       if (tiled && SC != 0)
         return fail(FM_E_UNSUPPORTED, "the tiled product layout needs tensor scales");
-      if (fmt == FM_E4M3)
-        gemm_wide8_kernel<FM_E4M3, SC><<<grid, wide8::NT, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, T, tiled);
-      else
-        gemm_wide8_kernel<FM_E5M2, SC><<<grid, wide8::NT, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, T, tiled);
+#define FM_WIDE8(F, W)                                                                          \
+  gemm_wide8_kernel<F, SC, W><<<grid, wide8::NT, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, \
+                                                          tn, T, tiled)
+      if (fmt == FM_E4M3) {
+        if (wn == 4) FM_WIDE8(FM_E4M3, 4);
+        else FM_WIDE8(FM_E4M3, 2);
+      } else {
+        if (wn == 4) FM_WIDE8(FM_E5M2, 4);
+        else FM_WIDE8(FM_E5M2, 2);
+      }
+#undef FM_WIDE8
       return launched("gemm_wide8_kernel");
     }
   }

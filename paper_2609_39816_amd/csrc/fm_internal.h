@@ -171,31 +171,30 @@ int launch_block_gemm(const uint8_t* Tq, const uint8_t* Sq, const float* dT, con
                       float* Mout, int batch, int Mb, int Nb, int Kb, int fmt, int scale_mode,
                       hipStream_t st, bool out_bf16 = false, bool tiled = false);
 
-// Rows of the output tile of the block-product kernel launch_block_gemm
-// runs for these arguments: 512 (gemm_wide_kernel: bf16 arithmetic, tensor
-// or row/column scales, fp32 products, Mb a multiple of 512, Nb of 128, Kb
-// of 64), 256 (gemm_dma_kernel: Kb a multiple of 128), 0 otherwise.  Tiles
-// are 128 columns wide.
+// Rows of the pieces of the tiled layout (below) of the block-product kernel
+// launch_block_gemm runs for these arguments: 128 (gemm_wide8_kernel: bf16
+// arithmetic, tensor or row/column scales, fp32 products, whole 256 x 256 or
+// 512 x 128 tiles, Kb a multiple of 64), 256 (gemm_dma_kernel: Kb a multiple
+// of 128), 0 otherwise.
 int block_gemm_tile_rows(int Mb, int Nb, int Kb, int scale_mode, bool out_bf16);
 
-// The tiled layout of a product block (Mb x Nb, whole TR x 128 tiles, TR =
-// 256 or 512): the 16-byte piece p (4 consecutive columns of one row) sits
-// at byte 16 p, t being the tile (row-major over the block's tiles).  For
-// TR = 256, p = (((t 8 + w) 4 + i) 4 + j) 64 + 4 l + c with the 64 x 64
-// quarter w = 2 (row / 64 % 4) + (column / 64 % 2), i = row / 16 % 4, j =
-// column / 16 % 4, l = row % 16 and c = column / 4 % 4.  For TR = 512, p =
-// ((((t 4 + w) 4 + i) 4 + j) 4 + g) 64 + 32 h + r with the 128-row quarter
-// w = row / 128 % 4, i = row / 32 % 4, r = row % 32, j = column / 32 % 4,
-// g = column / 8 % 4 and h = column / 4 % 2.  The block-product kernel
-// stores each wave's piece of a tile as one contiguous kilobyte; the
-// reconstruction reads pieces in this order.
+// The tiled layout of a product block (Mb x Nb, whole TR x 128 pieces, TR =
+// 256 or 128): the 16 bytes p (4 consecutive columns of one row) sit at byte
+// 16 p, t being the piece (row-major over the block's pieces).  For TR = 256,
+// p = (((t 8 + w) 4 + i) 4 + j) 64 + 4 l + c with the 64 x 64 quarter w = 2
+// (row / 64 % 4) + (column / 64 % 2), i = row / 16 % 4, j = column / 16 % 4,
+// l = row % 16 and c = column / 4 % 4.  For TR = 128, p = (((t 4 + i) 4 + j)
+// 4 + g) 64 + 32 h + r with i = row / 32 % 4, r = row % 32, j = column / 32
+// % 4, g = column / 8 % 4 and h = column / 4 % 2.  The block-product kernel
+// stores each wave's values of a tile in contiguous kilobytes; the
+// reconstruction reads them in this order.
 __host__ __device__ inline void tile_layout_position(int p, int Nb, int TR, int& row, int& col) {
   const int tn = Nb / 128;
-  if (TR == 512) {
+  if (TR == 128) {
     const int r = p & 31, h = (p >> 5) & 1, g = (p >> 6) & 3, j = (p >> 8) & 3;
-    const int i = (p >> 10) & 3, w = (p >> 12) & 3;
-    const int t = p >> 14, tm = t / tn;
-    row = tm * 512 + w * 128 + i * 32 + r;
+    const int i = (p >> 10) & 3;
+    const int t = p >> 12, tm = t / tn;
+    row = tm * 128 + i * 32 + r;
     col = (t - tm * tn) * 128 + j * 32 + 8 * g + 4 * h;
   } else {
     const int l = (p >> 2) & 15, c = p & 3;
@@ -221,7 +220,7 @@ struct ReconArgs {
   const float* rowscale = nullptr;  // optional: output row i*Mb + x times rowscale[i*Mb + x]
   int prod_bf16 = 0;  // products stored as bf16 (uint16_t at Mprod; group scales)
   int tiled = 0;      // products in the tiled layout of tiles of this many rows
-                      // (256 or 512; fp32, 4 positions per thread), or 0
+                      // (256 or 128; fp32), or 0
 };
 // Positions per thread in the reconstruction kernels (4 or 1) and the
 // number of workgroups per gauge (one position group per thread).
