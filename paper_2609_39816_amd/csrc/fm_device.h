@@ -303,15 +303,21 @@ __device__ __forceinline__ void form_encode_store(__amdgpu_buffer_rsrc_t rsrc, u
 }
 
 // Gauges g0 <= g < g1 of a at one position group (operand values xv); mode
-// 0 keeps its maxima in the LDS slots of gauge g - g0.
-template <class P, int VW, int MODE, int FMT, bool ROWS>
+// 0 keeps its maxima in the LDS slots of gauge g - g0.  GRAN: 0 one scale per
+// tensor, otherwise a.gran (in mode 1, 1 for 1 and 2 alike).  With GRAN > 0,
+// mode 0: `cells` groups per product in the slots, this lane's in `cell`, and `span`
+// lanes to a group (form_group_max_kernel).
+template <class P, int VW, int MODE, int FMT, int GRAN>
 __device__ __forceinline__ void form_static_gauges(const FormArgs& a, int g0, int g1,
                                                    const float (&xv)[P::NB][VW], bool active,
-                                                   int x, int y0, uint32_t voff, uint32_t* smax) {
+                                                   int x, int y0, uint32_t voff, uint32_t* smax,
+                                                   [[maybe_unused]] int cells = 1,
+                                                   [[maybe_unused]] int cell = 0,
+                                                   [[maybe_unused]] int span = 16) {
+  constexpr bool ROWS = GRAN != 0;
   constexpr int GR = 8, NG = (P::R + GR - 1) / GR;
   const int lane = threadIdx.x & 63;
   const uint32_t bsz = (uint32_t)a.br * (uint32_t)a.bc;
-  [[maybe_unused]] const int bcv = a.bc / VW;
   {
     // finer granularities: the position's offset among a product's groups
     [[maybe_unused]] const uint32_t gspan = ROWS ? group_span(a) : 0u;
@@ -323,6 +329,10 @@ __device__ __forceinline__ void form_static_gauges(const FormArgs& a, int g0, in
       if constexpr (MODE == 1)
         rsrc = __builtin_amdgcn_make_buffer_rsrc(a.codes + (size_t)g * P::R * bsz, (short)0,
                                                  (int)(P::R * bsz), 0x00020000);
+      [[maybe_unused]] __amdgpu_buffer_rsrc_t mrsrc;
+      if constexpr (GRAN == 2)
+        mrsrc = __builtin_amdgcn_make_buffer_rsrc(a.amax + (size_t)g * P::R * gspan, (short)0,
+                                                  (int)(P::R * gspan * 4u), 0x00020000);
       sfor<0, NG>([&](auto gc) {
         constexpr int gi = decltype(gc)::value;
         uint32_t lm[GR];
@@ -353,7 +363,7 @@ __device__ __forceinline__ void form_static_gauges(const FormArgs& a, int g0, in
 #pragma unroll
               for (int v = 0; v < VW; ++v) acc[v] = __builtin_fmaf(c, xv[b][v], acc[v]);
             });
-            if (ROWS && a.gran == 3) round_bf16<VW>(acc);
+            if constexpr (GRAN == 3) round_bf16<VW>(acc);
             if constexpr (MODE == 0) {
               // largest magnitude, NaN-propagating (v_maximum3_f32 on
               // absolute values: half an instruction per value); as bits it
@@ -371,48 +381,47 @@ __device__ __forceinline__ void form_static_gauges(const FormArgs& a, int g0, in
           }
         });
         if constexpr (MODE == 0 && ROWS) {
-          // one maximum per group, folded into global memory: when a group
-          // spans whole 16-lane DPP rows (bcv a multiple of 16, and 16 VW
-          // entries within one group of 128 for the finer granularities)
-          // they are reduced first and their last lane folds the result;
-          // the same with 8-lane halves of a row when 8 VW = 128 (the
-          // shifts by 1, 2, 4 leave lanes 7 and 15 with their half's
-          // maximum); otherwise every lane folds its own
+          // one maximum per group.  Lanes that share a group are reduced
+          // first with interleaved DPP row shifts (lane span - 1 of each
+          // `span` lanes then holds their maximum): 16 positions of a 128 x
+          // 128 tile, which is one group; otherwise the largest of 16, 8 and
+          // 4 that divides a row's position count (a group of 1 x 128 is at
+          // most 16 lanes then, and complete: it is stored as it is)
           constexpr int NJ = (gi * GR + GR <= P::R) ? GR : P::R - gi * GR;
-          if (VW == 16 && a.gran != 1 && bcv % 8 == 0) {
-            sfor<0, 3>([&](auto sc) {
-              constexpr int ctl = 0x111 + (1 << decltype(sc)::value) - 1;  // row_shr:1,2,4
-              uint32_t sh[NJ];
-#pragma unroll
-              for (int j = 0; j < NJ; ++j)
-                sh[j] = (uint32_t)__builtin_amdgcn_mov_dpp((int)lm[j], ctl, 0xf, 0xf, true);
-#pragma unroll
-              for (int j = 0; j < NJ; ++j) lm[j] = max(lm[j], sh[j]);
-            });
-            if ((lane & 7) == 7 && active) {
-#pragma unroll
-              for (int j = 0; j < NJ; ++j)
-                if (lm[j]) atomicMax(&a.amax[gidx(g, gi * GR + j)], lm[j]);
-            }
-          } else if (bcv % 16 == 0 && (a.gran == 1 || 16 * VW <= 128)) {
-            sfor<0, 4>([&](auto sc) {
-              constexpr int ctl = 0x111 + (1 << decltype(sc)::value) - 1;  // row_shr:1,2,4,8
-              uint32_t sh[NJ];
-#pragma unroll
-              for (int j = 0; j < NJ; ++j)
-                sh[j] = (uint32_t)__builtin_amdgcn_mov_dpp((int)lm[j], ctl, 0xf, 0xf, true);
-#pragma unroll
-              for (int j = 0; j < NJ; ++j) lm[j] = max(lm[j], sh[j]);
-            });
-            if ((lane & 15) == 15 && active) {
-#pragma unroll
-              for (int j = 0; j < NJ; ++j)
-                if (lm[j]) atomicMax(&a.amax[gidx(g, gi * GR + j)], lm[j]);
-            }
-          } else if (active) {
+          constexpr int kRow128 = 128 / VW;  // lanes per 128 entries
+          auto shift = [&](auto sc) {
+            constexpr int ctl = 0x111 + (1 << decltype(sc)::value) - 1;  // row_shr:1,2,4,8
+            uint32_t sh[NJ];
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-              if (lm[j]) atomicMax(&a.amax[gidx(g, gi * GR + j)], lm[j]);
+              sh[j] = (uint32_t)__builtin_amdgcn_mov_dpp((int)lm[j], ctl, 0xf, 0xf, true);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) lm[j] = max(lm[j], sh[j]);
+          };
+          if (span >= 4) {
+            shift(std::integral_constant<int, 0>{});
+            shift(std::integral_constant<int, 1>{});
+          }
+          if (span >= 8) shift(std::integral_constant<int, 2>{});
+          if (span >= 16) shift(std::integral_constant<int, 3>{});
+          const bool last = (lane & (span - 1)) == span - 1 && active;
+          if constexpr (GRAN == 2 && kRow128 <= 16) {
+            // (offset past the end: the store is dropped)
+            const uint32_t mo = last ? gloc * 4u : 0x80000000u;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+              __builtin_amdgcn_raw_buffer_store_b32(lm[j], mrsrc, (int)mo,
+                                                    (int)((uint32_t)(gi * GR + j + so) * gspan * 4u), 0);
+          } else if (last) {
+            if constexpr (GRAN == 2) {
+#pragma unroll
+              for (int j = 0; j < NJ; ++j)
+                if (lm[j]) atomicMax(&a.amax[gidx(g, gi * GR + j)], lm[j]);
+            } else {
+              uint32_t* slot = smax + ((size_t)(g - g0) * P::R + gi * GR) * cells + cell;
+#pragma unroll
+              for (int j = 0; j < NJ; ++j) atomicMax(slot + j * cells, lm[j]);
+            }
           }
         }
         if constexpr (MODE == 0 && !ROWS) {
@@ -537,7 +546,7 @@ __device__ __forceinline__ void form_trie_gauges(const FormArgs& a, int g0, int 
   }
 }
 
-template <class P, int VW, int MODE, int FMT, bool ROWS>
+template <class P, int VW, int MODE, int FMT, int GRAN>
 __device__ __forceinline__ void form_static_body(const FormArgs& a, int gpb, uint32_t* smax) {
   const int bcv = a.bc / VW;
   const int Ptot = a.br * bcv;
@@ -552,24 +561,23 @@ __device__ __forceinline__ void form_static_body(const FormArgs& a, int gpb, uin
     float xv[P::NB][VW];
     form_load<P::NB, VW>(a, xv, active, x, y0);
     [[maybe_unused]] uint64_t applied = 0;
-    if constexpr (P::TRIE && !ROWS)
+    if constexpr (P::TRIE && GRAN == 0)
       form_trie_gauges<P, VW, MODE, FMT>(a, g0, g1, xv, applied, active, voff, smax);
     else
-      form_static_gauges<P, VW, MODE, FMT, ROWS>(a, g0, g1, xv, active, x, y0, voff, smax);
+      form_static_gauges<P, VW, MODE, FMT, GRAN>(a, g0, g1, xv, active, x, y0, voff, smax);
   }
 }
 
-template <class P, int VW, int MODE, bool ROWS>
+template <class P, int VW, int MODE, int GRAN>
 __global__ __launch_bounds__(kThreads) void form_static_kernel(FormArgs a, int gpb) {
   extern __shared__ uint32_t smax[];  // mode 0: [gauge][product][wave * 4 + row]
   const int g0 = blockIdx.y * gpb;
   const int g1 = min(a.G, g0 + gpb);
-  if constexpr (MODE == 0 && ROWS) {
-    form_static_body<P, VW, 0, FM_E4M3, true>(a, gpb, smax);
-  } else if constexpr (MODE == 0) {
+  static_assert(MODE == 1 || GRAN == 0, "finer maxima: form_group_max_kernel");
+  if constexpr (MODE == 0) {
     for (int i = threadIdx.x; i < gpb * P::R * 16; i += kThreads) smax[i] = 0u;
     __syncthreads();
-    form_static_body<P, VW, 0, FM_E4M3, false>(a, gpb, smax);
+    form_static_body<P, VW, 0, FM_E4M3, 0>(a, gpb, smax);
     __syncthreads();
     const int n = (g1 - g0) * P::R;
     for (int k = threadIdx.x; k < n; k += kThreads) {
@@ -579,8 +587,58 @@ __global__ __launch_bounds__(kThreads) void form_static_kernel(FormArgs a, int g
       if (m) atomicMax(&a.amax[(size_t)g0 * P::R + k], m);
     }
   } else {
-    if (a.fmt == FM_E4M3) form_static_body<P, VW, 1, FM_E4M3, ROWS>(a, gpb, smax);
-    else form_static_body<P, VW, 1, FM_E5M2, ROWS>(a, gpb, smax);
+    if (a.fmt == FM_E4M3) form_static_body<P, VW, 1, FM_E4M3, GRAN>(a, gpb, smax);
+    else form_static_body<P, VW, 1, FM_E5M2, GRAN>(a, gpb, smax);
+  }
+}
+
+// Maxima of the finer granularities.  A workgroup takes a tile of tr rows x
+// tc columns of the block-sum tensors and the gauges of its slice; its maxima
+// wait in LDS, one slot per (gauge, product, group), and leave it once:
+//   gran 1 (a group is a row): whole rows, so the maxima are stored;
+//   gran 2 (1 x 128): complete within 16 lanes, stored straight from them
+//     (folded into global memory where 128 entries are more than 16 lanes);
+//   gran 3 (128 x 128 blocks): tr rows of one block, stored when that is all
+//     128, folded into global memory otherwise.
+// Bound by vector arithmetic like the encoding pass beside it.  Folding every
+// 16 lanes' (or every lane's) maximum into global memory instead had made
+// the atomics the bound: 512 gauges of 128 x 128 by row 146 us a side (the
+// encoding 16), 24 gauges of two-level 2048 x 4096 by group 366 us.
+template <class P, int VW, int GRAN>
+__global__ __launch_bounds__(kThreads) void form_group_max_kernel(FormArgs a, int gpb, int tr,
+                                                                  int tc, int cells, int span) {
+  extern __shared__ uint32_t smax[];
+  const int g0 = blockIdx.y * gpb, g1 = min(a.G, g0 + gpb);
+  const int tiles_c = a.bc / tc;
+  const int x0 = (int)blockIdx.x / tiles_c * tr, c0 = ((int)blockIdx.x % tiles_c) * tc;
+  const int rows = min(tr, a.br - x0);
+  const int tcv = tc / VW, n = rows * tcv;
+  if constexpr (GRAN != 2) {
+    for (int i = threadIdx.x; i < gpb * P::R * cells; i += kThreads) smax[i] = 0u;
+    __syncthreads();
+  }
+  for (int base = 0; base < n; base += kThreads) {
+    const int p = base + threadIdx.x;
+    const bool active = p < n;
+    const int xl = active ? p / tcv : 0;
+    const int x = x0 + xl, y0 = c0 + (active ? (p - xl * tcv) * VW : 0);
+    float xv[P::NB][VW];
+    form_load<P::NB, VW>(a, xv, active, x, y0);
+    form_static_gauges<P, VW, 0, FM_E4M3, GRAN>(a, g0, g1, xv, active, x, y0, 0u, smax,
+                                                      cells, GRAN == 1 ? xl : 0, span);
+  }
+  if constexpr (GRAN == 2) return;
+  __syncthreads();
+  const int total = (g1 - g0) * P::R * cells;
+  for (int i = threadIdx.x; i < total; i += kThreads) {
+    const int k = i / cells, c = i - k * cells;
+    if constexpr (GRAN == 1) {
+      if (c < rows) a.amax[(size_t)(g0 * P::R + k) * a.br + x0 + c] = smax[i];
+    } else {
+      uint32_t* dst = a.amax + group_index(a, g0, k, x0, c0);
+      if (tr == 128) *dst = smax[i];
+      else if (smax[i]) atomicMax(dst, smax[i]);
+    }
   }
 }
 
@@ -630,8 +688,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3, 8))
       form_trie_gauges<P, VW, 1, FMT>(aq, g0q, g1q, xv, applied, active, voff, smax);
       form_trie_gauges<P, VW, 0, FM_E4M3>(am, g0m, g1m, xv, applied, active, voff, smax);
     } else {
-      form_static_gauges<P, VW, 1, FMT, false>(aq, g0q, g1q, xv, active, x, y0, voff, smax);
-      form_static_gauges<P, VW, 0, FM_E4M3, false>(am, g0m, g1m, xv, active, x, y0, voff, smax);
+      form_static_gauges<P, VW, 1, FMT, 0>(aq, g0q, g1q, xv, active, x, y0, voff, smax);
+      form_static_gauges<P, VW, 0, FM_E4M3, 0>(am, g0m, g1m, xv, active, x, y0, voff, smax);
     }
   }
   __syncthreads();
@@ -984,20 +1042,70 @@ constexpr int static_vw() {
   return P::NB <= 4 ? 16 : (P::NB <= 16 ? 8 : 2);
 }
 
-template <class P, int MODE>
+// Tiles of form_group_max_kernel: enough rows to fill a workgroup (gran 1,
+// 2), or a block's 128 rows, fewer while the launch has less than 1024
+// workgroups (gran 3: down to 16, a workgroup's worth of positions); gauges
+// split over grid.y up to about 2048 workgroups, at most 48 KB of maxima each.
+template <class P, int SIDE>
+int launch_form_group_max(const FormArgs& a, hipStream_t st) {
+  constexpr int VW = static_vw<P>();
+  constexpr int kSlots = 12288;
+  const int bcv = a.bc / VW;
+  int tr, tc, cells = 1, span;
+  if (a.gran == 3) {
+    if (a.br % 128 || a.bc % 128) return fail(FM_E_SHAPE, "block scales need 128 x 128 blocks");
+    tr = 128, tc = 128, span = 16;
+    while (tr > 16 && (long long)(a.br / tr) * (a.bc / tc) * a.G < 1024) tr /= 2;
+  } else {
+    if (a.gran == 2 && a.bc % 128) return fail(FM_E_SHAPE, "group scales need whole groups of 128");
+    tc = a.bc;
+    tr = std::max(1, std::min(a.br, kThreads / bcv));
+    if (a.gran == 1) {
+      tr = std::min(tr, std::max(1, kSlots / P::R));
+      cells = tr;
+    }
+    span = bcv % 16 == 0 ? 16 : bcv % 8 == 0 ? 8 : bcv % 4 == 0 ? 4 : 1;
+    if (a.gran == 2) span = std::min(span, 128 / VW);
+  }
+  const long long tiles = (long long)((a.br + tr - 1) / tr) * (a.bc / tc);
+  const long long slices = std::max(1LL, std::min<long long>(a.G, (2048 + tiles - 1) / tiles));
+  int gpb = (int)((a.G + slices - 1) / slices);
+  gpb = std::max(1, std::min(gpb, kSlots / (P::R * cells)));
+  const int gy = (a.G + gpb - 1) / gpb;
+  if (tiles > 0x7fffffffLL || gy > 65535) return fail(FM_E_SHAPE, "too many maxima tiles");
+  const size_t shm = a.gran == 2 ? 0 : (size_t)gpb * P::R * cells * 4;
+  const dim3 grid((unsigned)tiles, gy);
+  // 1 x 128 groups are A's, 128 x 128 blocks B's
+  constexpr int FINE = SIDE == 0 ? 2 : 3;
+  if (a.gran != 1 && a.gran != FINE) return fail(FM_E_ARG, "granularity of the other side");
+  if (a.gran == 1)
+    form_group_max_kernel<P, VW, 1><<<grid, kThreads, shm, st>>>(a, gpb, tr, tc, cells, span);
+  else
+    form_group_max_kernel<P, VW, FINE><<<grid, kThreads, shm, st>>>(a, gpb, tr, tc, cells, span);
+  return launched("form_group_max_kernel");
+}
+
+template <class P, int MODE, int SIDE>
 int launch_form_static(const FormArgs& a, hipStream_t st) {
   constexpr int VW = static_vw<P>();
   int gpb;
-  if (a.per_row) {  // maxima go straight to global memory: no LDS table
-    const dim3 grid = form_grid(a, VW, a.G, gpb);
-    form_static_kernel<P, VW, MODE, true><<<grid, kThreads, 0, st>>>(a, gpb);
-    return launched("form_static_kernel");
+  if (a.per_row) {
+    if constexpr (MODE == 0) {
+      return launch_form_group_max<P, SIDE>(a, st);
+    } else {
+      const dim3 grid = form_grid(a, VW, a.G, gpb);
+      if (SIDE == 1 && a.gran == 3)
+        form_static_kernel<P, VW, 1, SIDE == 1 ? 3 : 1><<<grid, kThreads, 0, st>>>(a, gpb);
+      else
+        form_static_kernel<P, VW, 1, 1><<<grid, kThreads, 0, st>>>(a, gpb);
+      return launched("form_static_kernel");
+    }
   }
   // mode 0 LDS: 16 row slots per (gauge, product), at most 48 KB
   const int max_gpb = MODE == 0 ? std::max(1, 12288 / (P::R * 16)) : a.G;
   const dim3 grid = form_grid(a, VW, max_gpb, gpb);
   const size_t shm = (MODE == 0) ? (size_t)gpb * P::R * 16 * 4 : 0;
-  form_static_kernel<P, VW, MODE, false><<<grid, kThreads, shm, st>>>(a, gpb);
+  form_static_kernel<P, VW, MODE, 0><<<grid, kThreads, shm, st>>>(a, gpb);
   return launched("form_static_kernel");
 }
 
@@ -1129,12 +1237,12 @@ FM_PATTERN_FAMILIES(FM_DECLARE_FAMILY)
     using namespace dev;                                                             \
     if (side == 0) {                                                                 \
       if (!static_ok<pat::P::A>(a)) return 1;                                        \
-      return mode ? launch_form_static<pat::P::A, 1>(a, st)                          \
-                  : launch_form_static<pat::P::A, 0>(a, st);                         \
+      return mode ? launch_form_static<pat::P::A, 1, 0>(a, st)                          \
+                  : launch_form_static<pat::P::A, 0, 0>(a, st);                         \
     }                                                                                \
     if (!static_ok<pat::P::B>(a)) return 1;                                          \
-    return mode ? launch_form_static<pat::P::B, 1>(a, st)                            \
-                : launch_form_static<pat::P::B, 0>(a, st);                           \
+    return mode ? launch_form_static<pat::P::B, 1, 1>(a, st)                            \
+                : launch_form_static<pat::P::B, 0, 1>(a, st);                           \
   }                                                                                  \
   int form_merged_family_##P(const FormArgs& aq, const FormArgs& am, int side,       \
                              hipStream_t st) {                                       \
