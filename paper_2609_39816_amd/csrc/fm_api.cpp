@@ -90,20 +90,52 @@ struct Tables {
   std::vector<int> hpat;  // family of each gauge's H support (joint rounding only)
 };
 
-void append(Tables& T, const Lists& L, int R, const int nb[3]) {
-  const Side* src[3] = {&L.a, &L.b, &L.w};
+// The lists of one flattened scheme with their patterns and block signs.
+struct GaugeLists {
+  Lists L;
+  int pat[3];
+  bool trie[2];
+  uint64_t sgn[2];
+};
+
+void gauge_lists(const fm_scheme& f, GaugeLists& out) {
+  const int nb[3] = {f.m * f.k, f.n * f.k, f.m * f.n};
+  const double* mats[3] = {f.U.data(), f.V.data(), f.W.data()};
+  Side* sides[3] = {&out.L.a, &out.L.b, &out.L.w};
+  int pos[64];
+  bool all = true;
+  for (int k = 0; k < 3; ++k) {
+    out.pat[k] = -1;
+    if (nb[k] <= 64) {
+      // B's blocks are numbered (j, l), its coefficients stored (l, j)
+      for (int b = 0; b < nb[k]; ++b) pos[b] = k == 1 ? (b % f.k) * f.n + b / f.k : b;
+      out.pat[k] = gather_pattern(k, mats[k], f.R, nb[k], pos, *sides[k]);
+    }
+    all = all && out.pat[k] >= 0;
+  }
+  if (!all) {
+    build_lists(f, out.L);
+    for (int k = 0; k < 3; ++k) out.pat[k] = match_pattern(k, *sides[k], f.R, nb[k]);
+  }
+  for (int k = 0; k < 2; ++k) {
+    uint64_t m = 0;
+    out.trie[k] = block_signs(out.pat[k], k, *sides[k], nb[k], &m);
+    out.sgn[k] = out.trie[k] ? m : 0;
+  }
+}
+
+void append(Tables& T, const GaugeLists& gl, int R) {
+  const Side* src[3] = {&gl.L.a, &gl.L.b, &gl.L.w};
   for (int k = 0; k < 3; ++k) {
     Side& d = T.s[k];
     const int32_t base = (int32_t)d.idx.size();
     for (int r = 0; r <= R; ++r) d.off.push_back(base + src[k]->off[r]);
     d.idx.insert(d.idx.end(), src[k]->idx.begin(), src[k]->idx.end());
     d.coef.insert(d.coef.end(), src[k]->coef.begin(), src[k]->coef.end());
-    T.pat[k].push_back(match_pattern(k, *src[k], R, nb[k]));
+    T.pat[k].push_back(gl.pat[k]);
     if (k < 2) {
-      uint64_t m = 0;
-      const bool ok = block_signs(T.pat[k].back(), k, *src[k], nb[k], &m);
-      T.trie[k].push_back(ok ? 1 : 0);
-      T.sgn[k].push_back(ok ? m : 0);
+      T.trie[k].push_back(gl.trie[k] ? 1 : 0);
+      T.sgn[k].push_back(gl.sgn[k]);
     }
   }
   T.G += 1;
@@ -396,24 +428,65 @@ int check_ws(void* ws, size_t ws_bytes, size_t need) {
   return FM_OK;
 }
 
-// Appends the lists of gauges [g_from, g_to) to T.
+// Appends the lists of gauges [g_from, g_to) to T.  Gauges are independent:
+// up to 8 host threads take them in turn, one per 2^17 coefficients (about
+// 60 us of work, several times what starting a thread takes).
 int extend_tables(Tables& T, const fm_scheme* const* schemes, int g_from, int g_to, int levels,
                   const Geometry& geo) {
   T.R = geo.R;
-  for (int g = g_from; g < g_to; ++g) {
-    const fm_scheme* s = schemes[g];
-    if (!s) return fail(FM_E_ARG, "null scheme in orbit");
-    // one level: the scheme itself (no copy)
-    fm_scheme powered;
-    if (levels > 1) powered = power(*s, levels);
-    const fm_scheme& flat = levels > 1 ? powered : *s;
-    if (flat.m != geo.gm || flat.k != geo.gk || flat.n != geo.gn || flat.R != geo.R)
-      return fail(FM_E_MISMATCH, "schemes of one orbit must share grid and rank");
-    Lists L;
-    build_lists(flat, L);
-    const int nb[3] = {geo.NBa(), geo.NBb(), geo.NC()};
-    append(T, L, geo.R, nb);
+  const int n = g_to - g_from;
+  if (n <= 0) return FM_OK;
+  std::vector<GaugeLists> lists((size_t)n);
+  std::vector<int> rcs((size_t)n, FM_OK);
+  std::atomic<int> next{0};
+  auto work = [&] {
+    for (int i; (i = next.fetch_add(1)) < n;) {
+      // no exception may leave a worker thread
+      try {
+        const fm_scheme* s = schemes[g_from + i];
+        if (!s) {
+          rcs[i] = FM_E_ARG;
+          continue;
+        }
+        // one level: the scheme itself (no copy)
+        fm_scheme powered;
+        if (levels > 1) powered = power(*s, levels);
+        const fm_scheme& flat = levels > 1 ? powered : *s;
+        if (flat.m != geo.gm || flat.k != geo.gk || flat.n != geo.gn || flat.R != geo.R) {
+          rcs[i] = FM_E_MISMATCH;
+          continue;
+        }
+        gauge_lists(flat, lists[i]);
+      } catch (...) {
+        rcs[i] = FM_E_NOMEM;
+      }
+    }
+  };
+  const long long coeffs = (long long)n * geo.R * (geo.NBa() + geo.NBb() + geo.NC());
+  const int hw = std::max(1, (int)std::thread::hardware_concurrency());
+  const int nt = (int)std::min<long long>({8, hw, n, 1 + (coeffs >> 17)});
+  std::vector<std::thread> pool;
+  try {
+    for (int i = 1; i < nt; ++i) pool.emplace_back(work);
+  } catch (...) {
+    // fewer threads: the calling thread takes the rest
   }
+  work();
+  for (auto& th : pool) th.join();
+  for (int rc : rcs) {
+    if (rc == FM_E_ARG) return fail(rc, "null scheme in orbit");
+    if (rc == FM_E_MISMATCH) return fail(rc, "schemes of one orbit must share grid and rank");
+    if (rc) return fail(rc, "out of host memory");
+  }
+  for (int k = 0; k < 3; ++k) {
+    size_t entries = T.s[k].idx.size();
+    for (const GaugeLists& gl : lists)
+      entries += (k == 0 ? gl.L.a : k == 1 ? gl.L.b : gl.L.w).idx.size();
+    T.s[k].off.reserve(T.s[k].off.size() + (size_t)n * (geo.R + 1));
+    T.s[k].idx.reserve(entries);
+    T.s[k].coef.reserve(entries);
+  }
+  for (const GaugeLists& gl : lists) append(T, gl, geo.R);
   return FM_OK;
 }
 
@@ -465,46 +538,33 @@ int upload_table_range(const Tables& T, char* ws, const Layout& L, int g_from, i
 Tables make_tables(const fm_scheme* const* schemes, int G, int levels, const Geometry& geo,
                    int& rc) {
   Tables T;
-  T.R = geo.R;
-  rc = FM_OK;
-  for (int g = 0; g < G; ++g) {
-    const fm_scheme* s = schemes[g];
-    if (!s) {
-      rc = fail(FM_E_ARG, "null scheme in orbit");
-      return T;
-    }
-    fm_scheme flat = power(*s, levels);
-    if (flat.m != geo.gm || flat.k != geo.gk || flat.n != geo.gn || flat.R != geo.R) {
-      rc = fail(FM_E_MISMATCH, "schemes of one orbit must share grid and rank");
-      return T;
-    }
-    Lists L;
-    build_lists(flat, L);
-    const int nb[3] = {geo.NBa(), geo.NBb(), geo.NC()};
-    append(T, L, geo.R, nb);
-  }
+  rc = extend_tables(T, schemes, 0, G, levels, geo);
   return T;
 }
 
-int upload_tables(const Tables& T, char* ws, const Layout& L, hipStream_t st) {
-  // one contiguous region from the first table to the end of the last
+// Uploads every gauge's tables with one asynchronous copy, packed at the
+// start of the workspace's table region (which has room for dense lists: a
+// copy of it as laid out would move several times the tables' own bytes),
+// and moves L's table offsets there.
+int upload_tables(const Tables& T, char* ws, Layout& L, hipStream_t st) {
   const size_t base = L.off[0];
-  const size_t total = L.sg[1] + T.sgn[1].size() * 8 - base;
   std::vector<std::pair<const void*, size_t>> pieces;
   std::vector<size_t> offs;
+  size_t at = 0;
+  auto put = [&](const void* src, size_t bytes) {
+    pieces.push_back({src, bytes});
+    offs.push_back(at);
+    const size_t here = base + at;
+    at += up(bytes);
+    return here;
+  };
   for (int k = 0; k < 3; ++k) {
-    pieces.push_back({T.s[k].off.data(), T.s[k].off.size() * 4});
-    offs.push_back(L.off[k] - base);
-    pieces.push_back({T.s[k].idx.data(), T.s[k].idx.size() * 4});
-    offs.push_back(L.idx[k] - base);
-    pieces.push_back({T.s[k].coef.data(), T.s[k].coef.size() * 4});
-    offs.push_back(L.coef[k] - base);
+    L.off[k] = put(T.s[k].off.data(), T.s[k].off.size() * 4);
+    L.idx[k] = put(T.s[k].idx.data(), T.s[k].idx.size() * 4);
+    L.coef[k] = put(T.s[k].coef.data(), T.s[k].coef.size() * 4);
   }
-  for (int k = 0; k < 2; ++k) {
-    pieces.push_back({T.sgn[k].data(), T.sgn[k].size() * 8});
-    offs.push_back(L.sg[k] - base);
-  }
-  return upload(ws + base, pieces, offs, total, st);
+  for (int k = 0; k < 2; ++k) L.sg[k] = put(T.sgn[k].data(), T.sgn[k].size() * 8);
+  return upload(ws + base, pieces, offs, at, st);
 }
 
 // The prefix-shared chains for gauges [g0, g0 + n) of one side: the flag,
@@ -1195,7 +1255,7 @@ int fm_form_operands_scaled(const fm_scheme* s, int levels, const float* A, cons
   Geometry geo;
   if (int rc = check_geometry(s, levels, M, N, K, geo)) return rc;
   if (int rc = scale_shape_ok(geo.Mb, geo.Nb, geo.Kb, geo.R, scale_mode)) return rc;
-  const Layout L = make_layout(geo, 1, 1, true, scale_mode);
+  Layout L = make_layout(geo, 1, 1, true, scale_mode);
   if (int rc = check_ws(workspace, ws_bytes, L.total)) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
@@ -1264,7 +1324,7 @@ int fm_reconstruct(const fm_scheme* s, int levels, const float* Mprod, int M, in
   if (s)
     for (int l = 0; l < levels && gk <= 64; ++l) gk *= s->k;
   if (int rc = check_geometry(s, levels, M, N, (int)std::min<long long>(gk, 64) * 16, geo)) return rc;
-  const Layout L = make_layout(geo, 1, 1, false);
+  Layout L = make_layout(geo, 1, 1, false);
   if (int rc = check_ws(workspace, ws_bytes, L.total)) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
@@ -1289,7 +1349,7 @@ int fm_matmul_lowp_scaled(const fm_scheme* s, const float* A, const float* B, fl
   Geometry geo;
   if (int rc = check_geometry(s, levels, M, N, K, geo)) return rc;
   if (int rc = scale_shape_ok(geo.Mb, geo.Nb, geo.Kb, geo.R, scale_mode)) return rc;
-  const Layout L = make_layout(geo, 1, 1, true, scale_mode);
+  Layout L = make_layout(geo, 1, 1, true, scale_mode);
   if (int rc = check_ws(workspace, ws_bytes, L.total)) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;

@@ -64,6 +64,12 @@ void build_lists(const fm_scheme& flat, Lists& out);
 
 // Pattern family of one side of a list (compiled specializations), or -1.
 int match_pattern(int side, const Side& s, int R, int NB);
+// The list of one side straight from its coefficient matrix M (R x NB; block
+// b of row r at M[r NB + pos[b]]) when its fp32 nonzeros are exactly those of
+// a pattern: fills out as build_lists does and returns the pattern's id, else
+// -1 (out is then not meaningful).  One pass over M without a branch per
+// entry, five times faster than building the list and matching it.
+int gather_pattern(int side, const double* M, int R, int NB, const int* pos, Side& out);
 // Sign variants of a family with prefix-shared chains: true if every
 // coefficient of one scheme's side list (A: 0, B: 1) of family `pattern` is
 // the family's base coefficient times a sign that depends on its block

@@ -60,6 +60,36 @@ int match_pattern(int side, const Side& s, int R, int NB) {
   return -1;
 }
 
+int gather_pattern(int side, const double* M, int R, int NB, const int* pos, Side& out) {
+  bool any = false;
+  for (int p = 0; p < kNumPatterns; ++p)
+    any |= kPatterns[p].R == R && kPatterns[p].nb[side] == NB;
+  if (!any) return -1;
+  // (one rounding of every coefficient to fp32; a plain counting loop)
+  int nnz = 0;
+  const size_t n = (size_t)R * NB;
+  for (size_t i = 0; i < n; ++i) nnz += (float)M[i] != 0.0f ? 1 : 0;
+  for (int p = 0; p < kNumPatterns; ++p) {
+    const PatternRef& P = kPatterns[p];
+    if (P.R != R || P.nb[side] != NB || P.nnz[side] != nnz) continue;
+    // as many nonzeros as the pattern has entries, and none of the entries
+    // zero: the nonzeros are the entries
+    out.coef.resize(nnz);
+    bool ok = true;
+    for (int r = 0; r < R && ok; ++r)
+      for (int e = P.rowptr[side][r]; e < P.rowptr[side][r + 1]; ++e) {
+        const float f = (float)M[(size_t)r * NB + pos[P.idx[side][e]]];
+        out.coef[e] = f;
+        ok &= f != 0.0f;
+      }
+    if (!ok) continue;
+    out.off.assign(P.rowptr[side], P.rowptr[side] + R + 1);
+    out.idx.assign(P.idx[side], P.idx[side] + nnz);
+    return p;
+  }
+  return -1;
+}
+
 bool block_signs(int pattern, int side, const Side& s, int NB, uint64_t* mask) {
   if (pattern < 0 || pattern >= kNumPatterns || side < 0 || side > 1 || NB > 64) return false;
   const PatternRef& P = kPatterns[pattern];
