@@ -281,7 +281,7 @@ Layout make_layout(const Geometry& g, int G, int chunk, bool need_bt = true,
   L.recon_nblk = recon_blocks(ra);
   L.partial = take((size_t)chunk * L.recon_nblk * 8);
   L.errsq = take((size_t)G * 8);
-  L.out3 = take(3 * 8);
+  L.out3 = take(4 * 8);  // directly after errsq: read back together
   // repairs: A's rescaled rows and the row factors; every gauge's H
   L.arow = take(repair_rows(scale_mode) ? (size_t)g.M * g.K * 4 : 0);
   L.rowup = take(repair_rows(scale_mode) ? (size_t)g.M * 4 : 0);
@@ -1498,9 +1498,8 @@ int fm_orbit_eval_scaled(const fm_scheme* const* gauged, int G, const float* A, 
   } else if ((rc = upload_tables(T, ws, L, st))) {
     return rc;
   }
-  if ((rc = launch_fill_u32((uint32_t*)(ws + L.flags), 1, 0u, st))) return rc;
   float* Bt = (float*)(ws + L.bt);
-  if ((rc = launch_transpose(B, Bt, K, N, st))) return rc;
+  if ((rc = launch_transpose(B, Bt, K, N, st, (uint32_t*)(ws + L.flags)))) return rc;
   uint8_t* Tq = (uint8_t*)(ws + L.tq);
   uint8_t* Sq = (uint8_t*)(ws + L.sq);
   float* Mp = (float*)(ws + L.mprod);
@@ -1602,15 +1601,15 @@ int fm_orbit_eval_scaled(const fm_scheme* const* gauged, int G, const float* A, 
     if ((size_t)nblk * 3 * 8 > (size_t)chunk * geo.R * geo.Mb * geo.Nb * 4)
       return fail(FM_E_WORKSPACE, "workspace too small for the reference norm");
     if ((rc = launch_error_stats(nullptr, C_ref, nel, partial, st))) return rc;
-    if ((rc = launch_error_finalize(partial, nblk, (double*)(ws + L.out3), st))) return rc;
+    if ((rc = launch_error_finalize(partial, nblk, (double*)(ws + L.out3), st,
+                                    (const uint32_t*)(ws + L.flags))))
+      return rc;
   }
-  std::vector<double> h((size_t)G + 3 + 1);
-  if ((rc = download(h.data(), errsq, (size_t)G * 8, st))) return rc;
-  double o3[3];
-  if ((rc = download(o3, ws + L.out3, sizeof(o3), st))) return rc;
-  uint32_t flag = 0;
-  if ((rc = download(&flag, ws + L.flags, 4, st))) return rc;
-  if (flag) return fail(FM_E_NONFINITE, "a block sum was not finite");
+  // errors, the reference's sums and the flag in one copy
+  std::vector<double> h((L.out3 - L.errsq) / 8 + 4);
+  if ((rc = download(h.data(), errsq, h.size() * 8, st))) return rc;
+  const double* o3 = h.data() + (L.out3 - L.errsq) / 8;
+  if (o3[3] != 0.0) return fail(FM_E_NONFINITE, "a block sum was not finite");
   const double ref = std::sqrt(o3[1]);
   for (int g = 0; g < G; ++g) rel_fro_out[g] = ref > 0 ? std::sqrt(h[g]) / ref : 0.0;
   return FM_OK;

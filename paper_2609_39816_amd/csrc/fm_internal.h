@@ -109,7 +109,8 @@ void timing_end(int cls, hipStream_t st);
 int launch_fill_u32(uint32_t* p, size_t n, uint32_t value, hipStream_t st);
 
 // Bt (cols x rows) = X^T for X rows x cols, fp32.
-int launch_transpose(const float* X, float* Xt, int rows, int cols, hipStream_t st);
+int launch_transpose(const float* X, float* Xt, int rows, int cols, hipStream_t st,
+                     uint32_t* clear = nullptr);
 
 // Operand formation over a chunk of gauges (G gauges, lists already on the
 // device).  X: rows x cols fp32, grid gr x gc; off: G*(R+1) offsets into ent.
@@ -267,7 +268,8 @@ int launch_reference_f64(const float* A, const float* B, double* C, int M, int N
 int error_stats_blocks(size_t n);
 int launch_error_stats(const float* C, const double* Cref, size_t n, double* partial,
                        hipStream_t st);
-int launch_error_finalize(const double* partial, int nblk, double* out3, hipStream_t st);
+int launch_error_finalize(const double* partial, int nblk, double* out3, hipStream_t st,
+                          const uint32_t* flag = nullptr);
 
 // Diagnostic encoder: codes for n fp32 values with the kernels' encoder.
 int launch_fp8_encode(const float* x, uint8_t* out, size_t n, int fmt, int impl, hipStream_t st);

@@ -61,12 +61,14 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 
 // ------------------------------------------------------------- transpose
 // Xt (cols x rows) = X^T through a padded 32 x 32 LDS tile.
+// clear: a word set to zero on the way (or null).
 __global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict__ X,
                                                         float* __restrict__ Xt, int rows,
-                                                        int cols) {
+                                                        int cols, uint32_t* clear) {
   __shared__ float tile[32][33];
   const int c0 = blockIdx.x * 32, r0 = blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+  if (clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear = 0u;
   for (int k = 0; k < 32; k += 8) {
     const int r = r0 + ty + k, c = c0 + tx;
     if (r < rows && c < cols) tile[ty + k][tx] = X[(size_t)r * cols + c];
@@ -441,7 +443,8 @@ __global__ __launch_bounds__(kThreads) void error_stats_kernel(const float* __re
 }
 
 __global__ __launch_bounds__(64) void error_finalize_kernel(const double* partial, int nblk,
-                                                             double* out3) {
+                                                             double* out3,
+                                                             const uint32_t* flag) {
   if (blockIdx.x != 0) return;
   const int lane = threadIdx.x;
   double e = 0.0, r = 0.0, m = 0.0;
@@ -458,6 +461,7 @@ __global__ __launch_bounds__(64) void error_finalize_kernel(const double* partia
     out3[0] = e;
     out3[1] = r;
     out3[2] = m;
+    if (flag) out3[3] = (double)*flag;
   }
 }
 
@@ -471,9 +475,10 @@ int launch_fill_u32(uint32_t* p, size_t n, uint32_t value, hipStream_t st) {
   return launched("fill_u32_kernel");
 }
 
-int launch_transpose(const float* X, float* Xt, int rows, int cols, hipStream_t st) {
+int launch_transpose(const float* X, float* Xt, int rows, int cols, hipStream_t st,
+                     uint32_t* clear) {
   dim3 grid((cols + 31) / 32, (rows + 31) / 32);
-  transpose_kernel<<<grid, kThreads, 0, st>>>(X, Xt, rows, cols);
+  transpose_kernel<<<grid, kThreads, 0, st>>>(X, Xt, rows, cols, clear);
   return launched("transpose_kernel");
 }
 
@@ -561,8 +566,9 @@ int launch_error_stats(const float* C, const double* Cref, size_t n, double* par
   return launched("error_stats_kernel");
 }
 
-int launch_error_finalize(const double* partial, int nblk, double* out3, hipStream_t st) {
-  error_finalize_kernel<<<1, 64, 0, st>>>(partial, nblk, out3);
+int launch_error_finalize(const double* partial, int nblk, double* out3, hipStream_t st,
+                          const uint32_t* flag) {
+  error_finalize_kernel<<<1, 64, 0, st>>>(partial, nblk, out3, flag);
   return launched("error_finalize_kernel");
 }
 
