@@ -81,21 +81,56 @@ __global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict_
 }
 
 // ------------------------------------------------------------- repairs
-// Outside power-of-two row scaling (the repair rules): one wave per row t of
-// A computes the float64 sum of squares (lane l over the indices = l mod 64
+// Outside power-of-two row scaling (the repair rules): for row t of A a wave
+// computes the float64 sum of squares (lane l over the indices = l mod 64
 // in ascending order, then the fixed butterfly), m2 = sum / K, the least k
 // with 4^k >= m2 (at least -9; a non-finite row gets 0), writes
 // As[t] = A[t] * 2^-k and up[t] = 2^k.
-__global__ __launch_bounds__(kThreads) void row_repair_kernel(const float* __restrict__ A, int M,
-                                                              int K, float* __restrict__ As,
+// A workgroup of 4 waves per row: it loads 4096 values at once into LDS, one
+// wave runs the sum's fixed chain from there (which no more waves could
+// share), and all write the scaled row, from registers when it is no longer
+// than that.  Bound by memory latency and the chain.
+constexpr int kRepairLoads = 16, kRepairPiece = kThreads * kRepairLoads;
+__global__ __launch_bounds__(kThreads) void row_repair_kernel(const float* __restrict__ A, int K,
+                                                              float* __restrict__ As,
                                                               float* __restrict__ up) {
-  const int lane = threadIdx.x & 63;
-  const long long t = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-  if (t >= M) return;
-  const float* x = A + (size_t)t * K;
+  __shared__ float piece[kRepairPiece];
+  __shared__ double total;
+  const uint32_t n = (uint32_t)K;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const size_t t = blockIdx.x;
+  const float* x = A + t * K;
+  float* y = As + t * K;
+  float v[kRepairLoads];
+  auto load = [&](uint32_t i0) {
+#pragma unroll
+    for (int j = 0; j < kRepairLoads; ++j) {
+      const uint32_t i = i0 + kThreads * j + tid;
+      v[j] = x[i < n ? i : 0u];
+    }
+  };
   double s = 0.0;
-  for (int i = lane; i < K; i += 64) s += (double)x[i] * (double)x[i];
-  for (int off = 32; off > 0; off >>= 1) s = s + __shfl_xor(s, off, 64);
+  for (uint32_t i0 = 0; i0 < n; i0 += kRepairPiece) {
+    load(i0);
+    if (i0) __syncthreads();  // the chain is done with the piece before
+#pragma unroll
+    for (int j = 0; j < kRepairLoads; ++j) piece[kThreads * j + tid] = v[j];
+    __syncthreads();
+    if (tid < 64) {
+      const uint32_t m = min(n - i0, (uint32_t)kRepairPiece);
+#pragma unroll 16
+      for (uint32_t i = lane; i < m; i += 64) {
+        const double d = (double)piece[i];
+        s += d * d;
+      }
+    }
+  }
+  if (tid < 64) {
+    for (int off = 32; off > 0; off >>= 1) s = s + __shfl_xor(s, off, 64);
+    if (lane == 0) total = s;
+  }
+  __syncthreads();
+  s = total;
   const double m2 = s / (double)K;
   int k;
   if (!isfinite(m2)) {
@@ -110,9 +145,15 @@ __global__ __launch_bounds__(kThreads) void row_repair_kernel(const float* __res
     k = k < -9 ? -9 : k;
   }
   const float down = ldexpf(1.0f, -k);
-  float* y = As + (size_t)t * K;
-  for (int i = lane; i < K; i += 64) y[i] = x[i] * down;
-  if (lane == 0) up[t] = ldexpf(1.0f, k);
+  for (uint32_t i0 = 0; i0 < n; i0 += kRepairPiece) {
+    if (n > (uint32_t)kRepairPiece) load(i0);
+#pragma unroll
+    for (int j = 0; j < kRepairLoads; ++j) {
+      const uint32_t i = i0 + kThreads * j + tid;
+      if (i < n) y[i] = v[j] * down;
+    }
+  }
+  if (tid == 0) up[t] = ldexpf(1.0f, k);
 }
 
 // Joint rounding of B's bf16 block sums (the repair rules), one thread per
@@ -586,9 +627,8 @@ int launch_bf16_round(const float* x, float* out, size_t n, int impl, hipStream_
 }
 
 int launch_row_repair(const float* A, int M, int K, float* As, float* up, hipStream_t st) {
-  const long long blocks = ((long long)M + kThreads / 64 - 1) / (kThreads / 64);
-  if (M < 1 || K < 1 || blocks > 0x7fffffffLL) return fail(FM_E_SHAPE, "row repair shape");
-  row_repair_kernel<<<(unsigned)blocks, kThreads, 0, st>>>(A, M, K, As, up);
+  if (M < 1 || K < 1) return fail(FM_E_SHAPE, "row repair shape");
+  row_repair_kernel<<<(unsigned)M, kThreads, 0, st>>>(A, K, As, up);
   return launched("row_repair_kernel");
 }
 

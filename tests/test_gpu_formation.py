@@ -95,3 +95,28 @@ def test_orbit_gauges_share_workgroups(levels, mode, shape, G):
     for g in (0, 1, G // 2, G - 1):
         alone = fm.orbit_eval([orbit[g]], A, B, Cref, 1, scale_mode=sm)
         assert alone.view(np.uint64)[0] == errs.view(np.uint64)[g], g
+
+
+@pytest.mark.parametrize("K", [128, 896, 1024, 1152, 2048, 4224])
+def test_row_repair_lengths(K):
+    """Rows shorter than, as long as and longer than what a wave loads at
+    once, with squares that sum to a power of two and one unit beside it."""
+    from paper_2609_39816_amd import fm
+    rng = np.random.default_rng(K)
+    M, N = 24, 128
+    A = (rng.standard_normal((M, K)) * np.exp2(rng.integers(-6, 7, (M, 1)))).astype(np.float32)
+    A[3] = 0.0
+    A[4] = 0.25  # mean square exactly 2^-4
+    A[5] = 0.25
+    A[5, K - 1] = np.nextafter(np.float32(0.25), np.float32(1))
+    B = (0.02 * rng.standard_normal((K, N))).astype(np.float32)
+    k = oracle.row_exponents(A)
+    As = (A * np.exp2(-k.astype(np.float64))[:, None]).astype(np.float32)
+    s = fm.Scheme.base("classical")
+    Tq, _, dT, _ = fm.form_operands(s, torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), 1,
+                                    scale_mode=fm.SCALE_GROUP | fm.REPAIR_ROWS)
+    tabs, (gm, gk, _, _) = oracle.flatten_f32(osch.BASE_SCHEMES["classical"]())
+    tq, dt = oracle.form_operands(As, gm, gk, tabs[0], oracle.E4M3, scale_mode=oracle.SCALE_GROUP,
+                                  side=0)
+    assert np.array_equal(dT.cpu().numpy().view(np.uint32).reshape(-1), dt.view(np.uint32).reshape(-1))
+    assert np.array_equal(Tq.cpu().numpy(), tq)
