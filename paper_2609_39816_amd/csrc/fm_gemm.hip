@@ -5,6 +5,7 @@
 //  gemm_dma_kernel   persistent, 256 x 128 tiles, a 3-stage LDS ring filled
 //                    by direct global-to-LDS loads; inner lengths that are
 //                    multiples of 128.
+//  gemm_small_kernel one 32 x 32 tile per wave; products of at most 64 x 64.
 //  gemm_tile_kernel  one 128 x 128 tile per workgroup, double-buffered LDS;
 //                    any inner length that is a multiple of 16.
 #include <hip/hip_runtime.h>
@@ -192,6 +193,71 @@ __global__ __launch_bounds__(kThreads) void gemm_tile_kernel(const uint8_t* __re
         }
       }
     }
+}
+
+// Small products (at most 64 x 64; bf16 arithmetic): a wave per 32 x 32 tile,
+// its operand rows loaded straight into fragments.  Lane (r, h) = (lane % 32,
+// lane / 32) takes bytes [16 h, 16 h + 16) of row r per 32 of the inner
+// dimension, for both operands alike.  Such products are bound by launch and
+// memory, not by the matrix cores: a 128 x 128 tile would be mostly padding
+// (512 gauges of 49 products of 32 x 32 x 32: 282 us against 40).
+template <int FMT, int SC>
+__global__ __launch_bounds__(kThreads) void gemm_small_kernel(const uint8_t* __restrict__ Tq,
+                                                             const uint8_t* __restrict__ Sq,
+                                                             const float* __restrict__ dT,
+                                                             const float* __restrict__ dS,
+                                                             float* __restrict__ Mout, int Mb,
+                                                             int Nb, int Kb, int tiles_m,
+                                                             int tiles_n, long long total) {
+  typedef float acc16 __attribute__((ext_vector_type(16)));
+  const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+  const long long w = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  if (w >= total) return;
+  const int tiles = tiles_m * tiles_n;
+  const long long b = w / tiles;
+  const int t = (int)(w - b * tiles);
+  const int m0 = t / tiles_n * 32, n0 = (t - t / tiles_n * tiles_n) * 32;
+  // rows beyond the operand read row 0: they only feed outputs never stored
+  const int ar = m0 + r < Mb ? m0 + r : 0, br = n0 + r < Nb ? n0 + r : 0;
+  const uint8_t* pa = Tq + ((size_t)b * Mb + ar) * Kb + 16 * h;
+  const uint8_t* pb = Sq + ((size_t)b * Nb + br) * Kb + 16 * h;
+  acc16 acc;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+#pragma unroll 4
+  for (int k = 0; k < Kb; k += 32) {
+    uint4 a = make_uint4(0, 0, 0, 0), c = a;
+    if (k + 16 * h < Kb) {
+      a = *reinterpret_cast<const uint4*>(pa + k);
+      c = *reinterpret_cast<const uint4*>(pb + k);
+    }
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(widen8<FMT>((int)c.x, (int)c.y),
+                                                  widen8<FMT>((int)a.x, (int)a.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(widen8<FMT>((int)c.z, (int)c.w),
+                                                  widen8<FMT>((int)a.z, (int)a.w), acc, 0, 0, 0);
+  }
+  // element v of lane (r, h): row r, column 8 (v / 4) + 4 h + v % 4
+  const int row = m0 + r;
+  if (row >= Mb) return;
+  const float sT = SC ? dT[(size_t)b * Mb + row] : dT[b];
+  float* out = Mout + ((size_t)b * Mb + row) * Nb;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const int col = n0 + 8 * g + 4 * h;
+    float o[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float sS = SC ? dS[(size_t)b * Nb + (col + v < Nb ? col + v : 0)] : dS[b];
+      o[v] = (acc[4 * g + v] * sT) * sS;
+    }
+    if ((Nb & 3) == 0) {
+      if (col < Nb) *reinterpret_cast<float4*>(out + col) = make_float4(o[0], o[1], o[2], o[3]);
+    } else {
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+        if (col + v < Nb) out[col + v] = o[v];
+    }
+  }
 }
 
 // Pipelined persistent kernel (inner block length a multiple of 128):
@@ -1002,6 +1068,19 @@ int launch_block_gemm_sc(const uint8_t* Tq, const uint8_t* Sq, const float* dT, 
       }
 #undef FM_WIDE8
       return launched("gemm_wide8_kernel");
+    }
+  }
+  if constexpr (SC == 0 || SC == 1) {
+    if (Mb <= 64 && Nb <= 64 && !fp8acc && !tiled) {
+      const int tm = (Mb + 31) / 32, tn = (Nb + 31) / 32;
+      const long long total = (long long)batch * tm * tn;
+      const long long blocks = (total + kThreads / 64 - 1) / (kThreads / 64);
+      if (blocks > 0x7fffffffLL) return fail(FM_E_SHAPE, "too many GEMM tiles in one launch");
+      if (fmt == FM_E4M3)
+        gemm_small_kernel<FM_E4M3, SC><<<(unsigned)blocks, kThreads, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, total);
+      else
+        gemm_small_kernel<FM_E5M2, SC><<<(unsigned)blocks, kThreads, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, total);
+      return launched("gemm_small_kernel");
     }
   }
   if (Kb % GK == 0) {
