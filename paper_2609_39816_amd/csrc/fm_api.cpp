@@ -652,8 +652,31 @@ int form_codes_and_next_maxima(const Geometry& geo, const float* A, const float*
   return FM_OK;
 }
 
-// Operand formation for gauges [g0, g0 + n) of the uploaded tables.
-int form_chunk(const Geometry& geo, const float* A, const float* Bt, char* ws, const Layout& L,
+// Whether one scheme's side of B can be formed straight from B, without the
+// transposed copy (the joint rounding reads the copy).
+bool forms_from_b(const Geometry& geo, const Tables& T, const float* B, int scale_mode,
+                  uint8_t* Sq) {
+  if (T.G != 1 || repair_weights(scale_mode)) return false;
+  const int mode = base_mode(scale_mode);
+  FormArgs f{};
+  f.rows = geo.N;
+  f.cols = geo.K;
+  f.gr = geo.gn;
+  f.gc = geo.gk;
+  f.br = geo.Nb;
+  f.bc = geo.Kb;
+  f.R = geo.R;
+  f.G = 1;
+  f.codes = Sq;
+  f.per_row = mode == FM_SCALE_TENSOR ? 0 : 1;
+  f.gran = mode == FM_SCALE_GROUP ? 3 : 1;
+  return launch_form_direct(f, B, -1, chunk_pattern(T, 1, 0, 1), nullptr) == FM_OK;
+}
+
+// Operand formation for gauges [g0, g0 + n) of the uploaded tables.  Bd: B
+// itself where forms_from_b (one gauge), Bt then unused.
+int form_chunk(const Geometry& geo, const float* A, const float* Bt, const float* Bd, char* ws,
+               const Layout& L,
                const Tables& T, int g0, int n, int fmt, int scale_mode, uint8_t* Tq, uint8_t* Sq,
                float* dT, float* dS, hipStream_t st) {
   const int R = geo.R;
@@ -681,7 +704,9 @@ int form_chunk(const Geometry& geo, const float* A, const float* Bt, char* ws, c
   if (int rc = launch_fill_u32(amax, na + nb, 0u, st)) return rc;
   for (int side = 0; side < 2; ++side) {
     timing_begin(T_FORM_AMAX, st);
-    if (int rc = launch_form_runs(side ? fb : fa, 0, side, T, ws, L, g0, spans[side], st)) return rc;
+    if (int rc = side && Bd ? launch_form_direct(fb, Bd, 0, pb, st)
+                            : launch_form_runs(side ? fb : fa, 0, side, T, ws, L, g0, spans[side], st))
+      return rc;
     timing_end(T_FORM_AMAX, st);
   }
   if (int rc = launch_scales(amax, q, dd, (int)(na + nb), fmt, (uint32_t*)(ws + L.flags), st))
@@ -690,7 +715,9 @@ int form_chunk(const Geometry& geo, const float* A, const float* Bt, char* ws, c
   const int quant_sides = repair_weights(scale_mode) ? 1 : 2;
   for (int side = 0; side < quant_sides; ++side) {
     timing_begin(T_FORM_QUANT, st);
-    if (int rc = launch_form_runs(side ? fb : fa, 1, side, T, ws, L, g0, spans[side], st)) return rc;
+    if (int rc = side && Bd ? launch_form_direct(fb, Bd, 1, pb, st)
+                            : launch_form_runs(side ? fb : fa, 1, side, T, ws, L, g0, spans[side], st))
+      return rc;
     timing_end(T_FORM_QUANT, st);
   }
   if (repair_weights(scale_mode)) {
@@ -1265,10 +1292,11 @@ int fm_form_operands_scaled(const fm_scheme* s, int levels, const float* A, cons
   if (rc) return rc;
   if ((rc = upload_tables(T, ws, L, st))) return rc;
   float* Bt = (float*)(ws + L.bt);
-  if ((rc = launch_transpose(B, Bt, K, N, st))) return rc;
+  const bool direct = forms_from_b(geo, T, B, scale_mode, Sq);
+  if (!direct && (rc = launch_transpose(B, Bt, K, N, st))) return rc;
   const float *Aform, *rowup;
   if ((rc = prepare_repairs(geo, T, ws, L, scale_mode, A, Aform, rowup, st))) return rc;
-  return form_chunk(geo, Aform, Bt, ws, L, T, 0, 1, fmt, scale_mode, Tq, Sq, dT, dS, st);
+  return form_chunk(geo, Aform, Bt, direct ? B : nullptr, ws, L, T, 0, 1, fmt, scale_mode, Tq, Sq, dT, dS, st);
 } catch (...) {
   return host_failure();
 }
@@ -1359,13 +1387,14 @@ int fm_matmul_lowp_scaled(const fm_scheme* s, const float* A, const float* B, fl
   if (rc) return rc;
   if ((rc = upload_tables(T, ws, L, st))) return rc;
   float* Bt = (float*)(ws + L.bt);
-  if ((rc = launch_transpose(B, Bt, K, N, st))) return rc;
   uint8_t* Tq = (uint8_t*)(ws + L.tq);
   uint8_t* Sq = (uint8_t*)(ws + L.sq);
+  const bool direct = forms_from_b(geo, T, B, scale_mode, Sq);
+  if (!direct && (rc = launch_transpose(B, Bt, K, N, st))) return rc;
   const float *Aform, *rowup;
   if ((rc = prepare_repairs(geo, T, ws, L, scale_mode, A, Aform, rowup, st))) return rc;
-  if ((rc = form_chunk(geo, Aform, Bt, ws, L, T, 0, 1, fmt, scale_mode, Tq, Sq, nullptr, nullptr,
-                       st)))
+  if ((rc = form_chunk(geo, Aform, Bt, direct ? B : nullptr, ws, L, T, 0, 1, fmt, scale_mode, Tq, Sq,
+                       nullptr, nullptr, st)))
     return rc;
   const float* dd = (const float*)(ws + L.d);
   float* Mp = (float*)(ws + L.mprod);
@@ -1538,7 +1567,7 @@ int fm_orbit_eval_scaled(const fm_scheme* const* gauged, int G, const float* A, 
       if ((rc = form_codes_and_next_maxima(geo, Aform, Bt, ws, L, T, c, g0, n, n1, fmt, Tq, Sq,
                                            st)))
         return rc;
-    } else if ((rc = form_chunk(geo, Aform, Bt, ws, Lc, T, g0, n, fmt, scale_mode, Tq, Sq,
+    } else if ((rc = form_chunk(geo, Aform, Bt, nullptr, ws, Lc, T, g0, n, fmt, scale_mode, Tq, Sq,
                                 nullptr, nullptr, st))) {
       return rc;
     }

@@ -142,6 +142,11 @@ struct FormArgs {
 // pattern: family id from match_pattern (side A or B), or -1 for the
 // generic kernel.
 int launch_form(const FormArgs& a, int mode, int pattern, int side, hipStream_t st);
+// B's side of one scheme straight from B (K x N row-major, no transposed copy):
+// a as for launch_form on the copy, but for a.X; a.G = 1.  Returns 1, launching
+// nothing, when the arguments do not fit the family's direct kernels; mode -1
+// only asks.
+int launch_form_direct(const FormArgs& a, const float* B, int mode, int pattern, hipStream_t st);
 // One side's FP8 codes of one chunk (aq, scales known) and per-tensor maxima
 // of the next (am) in one pass; both of the family `pattern` (no generic
 // form).  Returns 1, launching nothing, when the pair does not fit the

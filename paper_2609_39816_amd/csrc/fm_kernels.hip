@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include "fm_device.h"
+#include "fm_direct.h"
 #include "fm_joint.h"
 
 
@@ -535,6 +536,16 @@ int launch_form(const FormArgs& a, int mode, int pattern, int side, hipStream_t 
   FM_PATTERN_FAMILIES(FM_FORM_CASE)
 #undef FM_FORM_CASE
   return launch_form_generic(a, mode, st);
+}
+
+int launch_form_direct(const FormArgs& a, const float* B, int mode, int pattern, hipStream_t st) {
+  int id = 0;
+#define FM_DIRECT_CASE(P)                                          \
+  if (pattern == id) return form_direct_family_##P(a, B, mode, st); \
+  ++id;
+  FM_PATTERN_FAMILIES(FM_DIRECT_CASE)
+#undef FM_DIRECT_CASE
+  return 1;
 }
 
 int launch_form_merged(const FormArgs& aq, const FormArgs& am, int pattern, int side,

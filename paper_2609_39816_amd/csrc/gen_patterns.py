@@ -286,9 +286,11 @@ def main():
         text = ("// Generated by gen_patterns.py: the specialized kernels of the " + name + "\n"
                 "// family.  Do not edit by hand.\n"
                 '#include "fm_device.h"\n'
+                '#include "fm_direct.h"\n'
                 '#include "fm_joint.h"\n\n'
                 "namespace fm {\n"
                 f"FM_DEFINE_FAMILY({name})\n"
+                f"FM_DEFINE_DIRECT({name})\n"
                 f"FM_DEFINE_JOINT({name})\n"
                 "}  // namespace fm\n")
         old = open(path).read() if os.path.exists(path) else None
