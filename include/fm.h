@@ -294,7 +294,7 @@ int fm_error_stats_noalloc(const float* C, const double* C_ref, int M, int N,
  * that stream (their reconstructions then run one after another).  The
  * results are the bits of the one-buffer schedule; within a chunk the
  * products may be stored in a tiled order internally (when they are whole
- * tiles of the block-product kernel, 512 x 128 or 256 x 128, with tensor
+ * tiles of the block-product kernel, 256 x 256, 512 x 128 or 256 x 128, with tensor
  * scales).  Synchronizes. */
 int fm_orbit_eval(const fm_scheme* const* gauged, int G, const float* A,
                   const float* B, const double* C_ref, int M, int N, int K,
