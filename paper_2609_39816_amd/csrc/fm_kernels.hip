@@ -335,9 +335,8 @@ __global__ __launch_bounds__(64) void reduce_rows_kernel(const double* partial, 
 // into LDS 58 and 64; this kernel 60 and 66; one wave of 64 x 128 per SIMD
 // no faster.  Products of two fp32 values are exact in
 // float64; the sums are float64, in ascending K steps of 4 for every output,
-// whatever the tiling.  VEC: whole tiles, K a multiple of 16 and 16-byte
-// aligned operands, so every load is a whole 16-byte piece; otherwise
-// guarded single loads (any shape and alignment).
+// whatever the tiling.  Whole tiles, K a multiple of 16 and 16-byte aligned
+// operands: every load is a whole 16-byte piece.
 // Lane l of a 16 x 16 x 4 step holds A[l % 16][l / 16] and B[l / 16][l % 16];
 // its four results v = 0..3 are rows l / 16 + 4 v, column l % 16 of the block
 // (checked on the device with small integer operands).  Row pitches: 32
@@ -347,7 +346,6 @@ __global__ __launch_bounds__(64) void reduce_rows_kernel(const double* partial, 
 typedef double v4d __attribute__((ext_vector_type(4)));
 typedef double v2d __attribute__((ext_vector_type(2)));
 constexpr int kRefThreads = 256;
-template <bool VEC>
 __global__ __launch_bounds__(kRefThreads, 2) void ref_f64_mfma_kernel(const float* __restrict__ A,
                                                                       const float* __restrict__ B,
                                                                       double* __restrict__ C, int M,
@@ -366,48 +364,30 @@ __global__ __launch_bounds__(kRefThreads, 2) void ref_f64_mfma_kernel(const floa
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
   float ra[NL], rb[NL];
-  // VEC: thread t loads 4 values from column 4 (t % 4) of A rows t / 4 and
-  // t / 4 + 64, and from column 4 (t % 32) of B rows t / 32 and t / 32 + 8;
-  // otherwise value i is A row t / 16 + 16 i, column t % 16, and B row
-  // t / 128 + 2 i, column t % 128
-  const int ar = VEC ? tid >> 2 : tid >> 4, ak = VEC ? (tid & 3) * 4 : tid & 15;
-  const int bk = VEC ? tid >> 5 : tid >> 7, bc = VEC ? (tid & 31) * 4 : tid & 127;
+  // thread t loads 4 values from column 4 (t % 4) of A rows t / 4 and
+  // t / 4 + 64, and from column 4 (t % 32) of B rows t / 32 and t / 32 + 8
+  const int ar = tid >> 2, ak = (tid & 3) * 4;
+  const int bk = tid >> 5, bc = (tid & 31) * 4;
   const float* Ap = A + (size_t)(m0 + ar) * K + ak;
   const float* Bp = B + (size_t)bk * N + n0 + bc;
   auto load = [&](int k0) {
-    if constexpr (VEC) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const float4 a4 = *reinterpret_cast<const float4*>(Ap + (size_t)64 * i * K + k0);
-        const float4 b4 = *reinterpret_cast<const float4*>(Bp + (size_t)(k0 + 8 * i) * N);
-        ra[4 * i] = a4.x, ra[4 * i + 1] = a4.y, ra[4 * i + 2] = a4.z, ra[4 * i + 3] = a4.w;
-        rb[4 * i] = b4.x, rb[4 * i + 1] = b4.y, rb[4 * i + 2] = b4.z, rb[4 * i + 3] = b4.w;
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        ra[i] = (m0 + ar + 16 * i < M && k0 + ak < K) ? Ap[(size_t)16 * i * K + k0] : 0.0f;
-        rb[i] = (k0 + bk + 2 * i < K && n0 + bc < N) ? Bp[(size_t)(k0 + 2 * i) * N] : 0.0f;
-      }
+    for (int i = 0; i < 2; ++i) {
+      const float4 a4 = *reinterpret_cast<const float4*>(Ap + (size_t)64 * i * K + k0);
+      const float4 b4 = *reinterpret_cast<const float4*>(Bp + (size_t)(k0 + 8 * i) * N);
+      ra[4 * i] = a4.x, ra[4 * i + 1] = a4.y, ra[4 * i + 2] = a4.z, ra[4 * i + 3] = a4.w;
+      rb[4 * i] = b4.x, rb[4 * i + 1] = b4.y, rb[4 * i + 2] = b4.z, rb[4 * i + 3] = b4.w;
     }
   };
   auto store = [&](int buf) {
-    if constexpr (VEC) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        v2d* pa = reinterpret_cast<v2d*>(&As[buf][ar + 64 * i][ak]);
-        v2d* pb = reinterpret_cast<v2d*>(&Bs[buf][bk + 8 * i][bc]);
-        pa[0] = (v2d){(double)ra[4 * i], (double)ra[4 * i + 1]};
-        pa[1] = (v2d){(double)ra[4 * i + 2], (double)ra[4 * i + 3]};
-        pb[0] = (v2d){(double)rb[4 * i], (double)rb[4 * i + 1]};
-        pb[1] = (v2d){(double)rb[4 * i + 2], (double)rb[4 * i + 3]};
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < NL; ++i) {
-        As[buf][ar + 16 * i][ak] = (double)ra[i];
-        Bs[buf][bk + 2 * i][bc] = (double)rb[i];
-      }
+    for (int i = 0; i < 2; ++i) {
+      v2d* pa = reinterpret_cast<v2d*>(&As[buf][ar + 64 * i][ak]);
+      v2d* pb = reinterpret_cast<v2d*>(&Bs[buf][bk + 8 * i][bc]);
+      pa[0] = (v2d){(double)ra[4 * i], (double)ra[4 * i + 1]};
+      pa[1] = (v2d){(double)ra[4 * i + 2], (double)ra[4 * i + 3]};
+      pb[0] = (v2d){(double)rb[4 * i], (double)rb[4 * i + 1]};
+      pb[1] = (v2d){(double)rb[4 * i + 2], (double)rb[4 * i + 3]};
     }
   };
   auto products = [&](int buf, int kk) {
@@ -445,6 +425,87 @@ __global__ __launch_bounds__(kRefThreads, 2) void ref_f64_mfma_kernel(const floa
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int col = n0 + wn * 64 + j * 16 + l16;
+        if (col < N) C[(size_t)row * N + col] = acc[i][j][v];
+      }
+    }
+}
+
+// The same sums for any shape and alignment, and for up to one tile per CU:
+// 8 waves of 64 x 32, so that a tile alone on its CU still has two waves per
+// SIMD (the kernel above would have one).  Guarded single loads, K step 64,
+// operands widened at every LDS read.  Against the kernel above with guarded
+// loads, a baseline call of 447 x 6512 x 1757 (56 tiles) 1117 against 1328
+// us, of 956 x 1520 x 1369 321 against 352.
+constexpr int kRefWideThreads = 512;
+__global__ __launch_bounds__(kRefWideThreads) void ref_f64_any_kernel(const float* __restrict__ A,
+                                                                   const float* __restrict__ B,
+                                                                   double* __restrict__ C, int M,
+                                                                   int N, int K) {
+  constexpr int KS = 64;  // K step
+  constexpr int NL = 128 * KS / kRefWideThreads;  // loads per thread and operand (16)
+  __shared__ float As[128][KS + 1];
+  __shared__ float Bs[KS][128 + 4];
+  const int m0 = blockIdx.y * 128, n0 = blockIdx.x * 128;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave >> 2, wn = wave & 3;  // 64-row half, 32-column quarter
+  const int l16 = lane & 15, lq = lane >> 4;
+  v4d acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
+  // the next step's operands are loaded into registers while this step's
+  // products run
+  float ra[NL], rb[NL];
+  auto load = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int idx = tid + kRefWideThreads * i;  // 0 .. 8191
+      const int r = idx >> 6, kk = idx & 63;
+      const int gr = m0 + r, gk = k0 + kk;
+      ra[i] = (gr < M && gk < K) ? A[(size_t)gr * K + gk] : 0.0f;
+      const int kb = idx >> 7, c = idx & 127;
+      const int gkb = k0 + kb, gc = n0 + c;
+      rb[i] = (gkb < K && gc < N) ? B[(size_t)gkb * N + gc] : 0.0f;
+    }
+  };
+  auto store = [&]() {
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int idx = tid + kRefWideThreads * i;
+      As[idx >> 6][idx & 63] = ra[i];
+      Bs[idx >> 7][idx & 127] = rb[i];
+    }
+  };
+  load(0);
+  for (int k0 = 0; k0 < K; k0 += KS) {
+    store();
+    __syncthreads();
+    if (k0 + KS < K) load(k0 + KS);
+#pragma unroll
+    for (int kk = 0; kk < KS; kk += 4) {
+      double a[4], b[2];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = (double)As[wm * 64 + i * 16 + l16][kk + lq];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) b[j] = (double)Bs[kk + lq][wn * 32 + j * 16 + l16];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int row = m0 + wm * 64 + i * 16 + lq + 4 * v;
+      if (row >= M) continue;
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int col = n0 + wn * 32 + j * 16 + l16;
         if (col < N) C[(size_t)row * N + col] = acc[i][j][v];
       }
     }
@@ -599,12 +660,14 @@ int launch_reduce_rows(const double* partial, int nblk, int G, double* out, hipS
 int launch_reference_f64(const float* A, const float* B, double* C, int M, int N, int K,
                          hipStream_t st) {
   dim3 grid((N + 127) / 128, (M + 127) / 128);
+  // 256 CUs: beyond one tile each, two workgroups of 4 waves share a CU
   const bool vec = M % 128 == 0 && N % 128 == 0 && K % 16 == 0 &&
-                   (((uintptr_t)A | (uintptr_t)B) & 15u) == 0;
+                   (((uintptr_t)A | (uintptr_t)B) & 15u) == 0 &&
+                   (long long)grid.x * grid.y > 256;
   if (vec)
-    ref_f64_mfma_kernel<true><<<grid, kRefThreads, 0, st>>>(A, B, C, M, N, K);
+    ref_f64_mfma_kernel<<<grid, kRefThreads, 0, st>>>(A, B, C, M, N, K);
   else
-    ref_f64_mfma_kernel<false><<<grid, kRefThreads, 0, st>>>(A, B, C, M, N, K);
+    ref_f64_any_kernel<<<grid, kRefWideThreads, 0, st>>>(A, B, C, M, N, K);
   return launched("ref_f64_mfma_kernel");
 }
 

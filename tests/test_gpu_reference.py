@@ -1,6 +1,7 @@
-"""The float64 reference kernel at the edges of its tiles: whole 128 x 128
-tiles with K steps of 16 take its 16-byte loads, anything else (a remainder
-in any dimension, a misaligned operand) its guarded ones."""
+"""The float64 reference kernel at the edges of its tiles: more than
+256 whole 128 x 128 tiles with K steps of 16 take the kernel with 16-byte
+loads, anything else (fewer tiles, a remainder in any dimension, a
+misaligned operand) the one with guarded loads."""
 import numpy as np
 import pytest
 
@@ -9,7 +10,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(128, 16, 128), (128, 48, 256), (384, 32, 128), (128, 17, 128), (129, 16, 128),
-          (128, 16, 127), (1, 1, 1), (3, 70, 260), (257, 33, 131)]
+          (128, 16, 127), (1, 1, 1), (3, 70, 260), (257, 33, 131), (2048, 32, 2048), (2176, 16, 2048),
+          (2176, 48, 2176)]
 
 
 @pytest.mark.parametrize("M,K,N", SHAPES)
