@@ -433,8 +433,8 @@ __global__ __launch_bounds__(kRefThreads, 2) void ref_f64_mfma_kernel(const floa
 // The same sums for any shape and alignment, and for up to one tile per CU:
 // 8 waves of 64 x 32, so that a tile alone on its CU still has two waves per
 // SIMD (the kernel above would have one).  Guarded single loads, K step 64,
-// operands widened at every LDS read.  Against the kernel above with guarded
-// loads, a baseline call of 447 x 6512 x 1757 (56 tiles) 1117 against 1328
+// operands widened at every LDS read.  Against 4 waves with clamped rows and
+// single loads, a baseline call of 447 x 6512 x 1757 (56 tiles) 1117 against 1328
 // us, of 956 x 1520 x 1369 321 against 352.
 constexpr int kRefWideThreads = 512;
 __global__ __launch_bounds__(kRefWideThreads) void ref_f64_any_kernel(const float* __restrict__ A,
