@@ -156,7 +156,7 @@ __device__ __forceinline__ void form_load(const FormArgs& a, float (&xv)[NB][VW]
 // (g R + r) group_span, and a part of the position alone, group_local:
 // the static kernels form the local part once per position group, so the
 // per-product address is one scalar product plus that offset.
-__device__ __forceinline__ uint32_t group_span(const FormArgs& a) {
+__host__ __device__ __forceinline__ uint32_t group_span(const FormArgs& a) {
   if (a.gran == 1) return (uint32_t)a.br;
   return (uint32_t)(a.bc / 128) * (uint32_t)(a.gran == 2 ? a.br : a.br / 128);
 }
@@ -1071,17 +1071,26 @@ int launch_form_group_max(const FormArgs& a, hipStream_t st) {
   const long long slices = std::max(1LL, std::min<long long>(a.G, (2048 + tiles - 1) / tiles));
   int gpb = (int)((a.G + slices - 1) / slices);
   gpb = std::max(1, std::min(gpb, kSlots / (P::R * cells)));
-  const int gy = (a.G + gpb - 1) / gpb;
-  if (tiles > 0x7fffffffLL || gy > 65535) return fail(FM_E_SHAPE, "too many maxima tiles");
+  if (tiles > 0x7fffffffLL) return fail(FM_E_SHAPE, "too many maxima tiles");
   const size_t shm = a.gran == 2 ? 0 : (size_t)gpb * P::R * cells * 4;
-  const dim3 grid((unsigned)tiles, gy);
   // 1 x 128 groups are A's, 128 x 128 blocks B's
   constexpr int FINE = SIDE == 0 ? 2 : 3;
   if (a.gran != 1 && a.gran != FINE) return fail(FM_E_ARG, "granularity of the other side");
-  if (a.gran == 1)
-    form_group_max_kernel<P, VW, 1><<<grid, kThreads, shm, st>>>(a, gpb, tr, tc, cells, span);
-  else
-    form_group_max_kernel<P, VW, FINE><<<grid, kThreads, shm, st>>>(a, gpb, tr, tc, cells, span);
+  // a launch for every 65535 slices, the most a grid holds along y (a slice
+  // can be one gauge: 49 products of 128 rows fill the LDS slots)
+  const int per = 65535;
+  for (int g0 = 0; g0 < a.G;) {
+    FormArgs f = a;
+    f.G = (int)std::min<long long>(a.G - g0, (long long)per * gpb);
+    f.off += (size_t)g0 * (P::R + 1);
+    f.amax += (size_t)g0 * P::R * group_span(a);
+    const dim3 grid((unsigned)tiles, (f.G + gpb - 1) / gpb);
+    if (a.gran == 1)
+      form_group_max_kernel<P, VW, 1><<<grid, kThreads, shm, st>>>(f, gpb, tr, tc, cells, span);
+    else
+      form_group_max_kernel<P, VW, FINE><<<grid, kThreads, shm, st>>>(f, gpb, tr, tc, cells, span);
+    g0 += f.G;
+  }
   return launched("form_group_max_kernel");
 }
 

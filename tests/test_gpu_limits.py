@@ -1,0 +1,27 @@
+"""Calls beyond the limits of one launch's grid."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import synthetic as sy
+
+pytestmark = pytest.mark.gpu
+
+
+def test_more_gauges_than_grid_slices():
+    """Per-row maxima of 128 block-sum rows take one gauge per slice: more
+    than 65535 gauges in one chunk.  Two schemes in turn: every error has the
+    bits of the orbit of the two."""
+    from paper_2609_39816_amd import fm
+    M, K, N, G = 512, 64, 4, 65600
+    rng = np.random.default_rng(8)
+    A = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).cuda()
+    B = torch.from_numpy(rng.standard_normal((K, N)).astype(np.float32)).cuda()
+    gs = [(np.diag(d), np.diag(e), np.diag(f)) for d, e, f in sy.sample_sign_orbit(4, 4, 4, 2, 4)]
+    pair = fm.Scheme.base("strassen").kron(2).gauge_orbit(gs)
+    Cref = fm.reference_f64(A, B)
+    want = fm.orbit_eval(pair, A, B, Cref, 1, scale_mode=fm.SCALE_ROWCOL)
+    errs = fm.orbit_eval(list(pair) * (G // 2), A, B, Cref, 1, scale_mode=fm.SCALE_ROWCOL)
+    assert np.array_equal(errs.view(np.uint64).reshape(-1, 2),
+                          np.broadcast_to(want.view(np.uint64), (G // 2, 2)))
