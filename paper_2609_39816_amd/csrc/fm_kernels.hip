@@ -92,14 +92,17 @@ __global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict_
 // share), and all write the scaled row, from registers when it is no longer
 // than that.  Bound by memory latency and the chain.
 constexpr int kRepairLoads = 16, kRepairPiece = kThreads * kRepairLoads;
-__global__ __launch_bounds__(kThreads) void row_repair_kernel(const float* __restrict__ A, int K,
-                                                              float* __restrict__ As,
+// Rows along x, then y (a grid holds fewer than 2^32 threads along x).
+constexpr int kRepairGridX = 1 << 20;
+__global__ __launch_bounds__(kThreads) void row_repair_kernel(const float* __restrict__ A, int M,
+                                                              int K, float* __restrict__ As,
                                                               float* __restrict__ up) {
   __shared__ float piece[kRepairPiece];
   __shared__ double total;
   const uint32_t n = (uint32_t)K;
   const int tid = threadIdx.x, lane = tid & 63;
-  const size_t t = blockIdx.x;
+  const size_t t = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+  if (t >= (size_t)M) return;
   const float* x = A + t * K;
   float* y = As + t * K;
   float v[kRepairLoads];
@@ -702,7 +705,9 @@ int launch_bf16_round(const float* x, float* out, size_t n, int impl, hipStream_
 
 int launch_row_repair(const float* A, int M, int K, float* As, float* up, hipStream_t st) {
   if (M < 1 || K < 1) return fail(FM_E_SHAPE, "row repair shape");
-  row_repair_kernel<<<(unsigned)M, kThreads, 0, st>>>(A, K, As, up);
+  const int gx = std::min(M, kRepairGridX);
+  const dim3 grid(gx, (unsigned)(((long long)M + gx - 1) / gx));
+  row_repair_kernel<<<grid, kThreads, 0, st>>>(A, M, K, As, up);
   return launched("row_repair_kernel");
 }
 

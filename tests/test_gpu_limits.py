@@ -25,3 +25,22 @@ def test_more_gauges_than_grid_slices():
     errs = fm.orbit_eval(list(pair) * (G // 2), A, B, Cref, 1, scale_mode=fm.SCALE_ROWCOL)
     assert np.array_equal(errs.view(np.uint64).reshape(-1, 2),
                           np.broadcast_to(want.view(np.uint64), (G // 2, 2)))
+
+
+def test_more_repaired_rows_than_one_grid_row():
+    """The row repair takes a workgroup per row: more than 2^24 rows.  Codes
+    and scales of the first and last rows are those of a call of them alone."""
+    from paper_2609_39816_amd import fm
+    M, K, N, n = (1 << 24) + 8, 128, 128, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(6)
+    A = torch.randn((M, K), generator=g, device="cuda")
+    A[-n:] *= torch.exp2(torch.arange(n, device="cuda") - 8.0)[:, None]
+    B = torch.randn((K, N), generator=g, device="cuda")
+    s = fm.Scheme.base("classical")
+    mode = fm.SCALE_GROUP | fm.REPAIR_ROWS
+    Tq, _, dT, _ = fm.form_operands(s, A, B, 1, scale_mode=mode)
+    for rows in (slice(0, n), slice(M - n, M)):
+        tq, _, dt, _ = fm.form_operands(s, A[rows].contiguous(), B, 1, scale_mode=mode)
+        assert torch.equal(Tq[:, rows], tq)
+        assert torch.equal(dT[:, :, rows].view(torch.int32), dt.view(torch.int32))
