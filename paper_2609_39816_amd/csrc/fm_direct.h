@@ -211,17 +211,18 @@ int launch_form_direct(const FormArgs& a, const float* B, int mode, hipStream_t 
         (a.per_row && a.gran == 3 && (Kb % 128 || Nb % 128)))
       return 1;
     const long long tz = (Nb + 31) / 32, tk = (Kb + 63) / 64;
-    if (tz * tk > 0x7fffffffLL) return 1;
+    // strips of at most 128 rows for the maxima, shorter while the launch has
+    // less than 1024 workgroups (but 16 rows: four per wave)
+    int strip = 128;
+    const int nz = (Nb + 127) / 128;
+    while (strip > 16 && (long long)nz * ((Kb + strip - 1) / strip) < 1024) strip /= 2;
+    const int strips = (Kb + strip - 1) / strip;
+    // a grid holds 65535 workgroups along y and fewer than 2^32 threads along x
+    if (strips > 65535 || tz * tk >= (1LL << 32) / 512) return 1;
     if (mode < 0) return FM_OK;
     const int gran = a.per_row ? a.gran : 0;
     if (mode == 0) {
-      // strips of at most 128 rows, shorter while the launch has less than
-      // 1024 workgroups (but 16 rows: four per wave)
-      int strip = 128;
-      const int nz = (Nb + 127) / 128;
-      while (strip > 16 && (long long)nz * ((Kb + strip - 1) / strip) < 1024) strip /= 2;
-      if ((Kb + strip - 1) / strip > 65535) return fail(FM_E_SHAPE, "too many rows");
-      const dim3 grid(nz, (Kb + strip - 1) / strip);
+      const dim3 grid(nz, strips);
       if (gran == 0) form_direct_max_kernel<P, 0><<<grid, kThreads, 0, st>>>(a, B, N, strip);
       else if (gran == 1) form_direct_max_kernel<P, 1><<<grid, kThreads, 0, st>>>(a, B, N, strip);
       else form_direct_max_kernel<P, 3><<<grid, kThreads, 0, st>>>(a, B, N, strip);

@@ -4,6 +4,8 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+import oracle
+from oracle import schemes as osch
 import synthetic as sy
 
 pytestmark = pytest.mark.gpu
@@ -44,3 +46,22 @@ def test_more_repaired_rows_than_one_grid_row():
         tq, _, dt, _ = fm.form_operands(s, A[rows].contiguous(), B, 1, scale_mode=mode)
         assert torch.equal(Tq[:, rows], tq)
         assert torch.equal(dT[:, :, rows].view(torch.int32), dt.view(torch.int32))
+
+
+def test_inner_length_beyond_the_direct_formation():
+    """B's operand is formed from the transposed copy where its rows are more
+    strips than the direct kernels' grid holds."""
+    from paper_2609_39816_amd import fm
+    M, K, N = 1, (1 << 23) + 128, 2
+    rng = np.random.default_rng(9)
+    A = rng.standard_normal((M, K)).astype(np.float32)
+    B = (0.02 * rng.standard_normal((K, N))).astype(np.float32)
+    Tq, Sq, dT, dS = fm.form_operands(fm.Scheme.base("classical"), torch.from_numpy(A).cuda(),
+                                      torch.from_numpy(B).cuda())
+    tabs, (gm, gk, gn, _) = oracle.flatten_f32(osch.BASE_SCHEMES["classical"]())
+    tq, dt = oracle.form_operands(A, gm, gk, tabs[0], oracle.E4M3, side=0)
+    sq, ds = oracle.form_operands(B, gk, gn, tabs[1], oracle.E4M3, side=1)
+    assert np.array_equal(dT.cpu().numpy(), dt.reshape(-1))
+    assert np.array_equal(dS.cpu().numpy(), ds.reshape(-1))
+    assert np.array_equal(Tq.cpu().numpy(), tq)
+    assert np.array_equal(Sq.cpu().numpy(), sq.transpose(0, 2, 1))
