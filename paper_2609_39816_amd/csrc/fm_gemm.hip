@@ -211,7 +211,8 @@ __global__ __launch_bounds__(kThreads) void gemm_small_kernel(const uint8_t* __r
                                                              int tiles_n, long long total) {
   typedef float acc16 __attribute__((ext_vector_type(16)));
   const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
-  const long long w = (long long)blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+  const long long blk = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+  const long long w = blk * (kThreads / 64) + (threadIdx.x >> 6);
   if (w >= total) return;
   const int tiles = tiles_m * tiles_n;
   const long long b = w / tiles;
@@ -1076,10 +1077,13 @@ int launch_block_gemm_sc(const uint8_t* Tq, const uint8_t* Sq, const float* dT, 
       const long long total = (long long)batch * tm * tn;
       const long long blocks = (total + kThreads / 64 - 1) / (kThreads / 64);
       if (blocks > 0x7fffffffLL) return fail(FM_E_SHAPE, "too many GEMM tiles in one launch");
+      // along x and y: a grid holds fewer than 2^32 threads along x
+      const unsigned gx = (unsigned)std::min<long long>(blocks, 1 << 20);
+      const dim3 grid(gx, (unsigned)((blocks + gx - 1) / gx));
       if (fmt == FM_E4M3)
-        gemm_small_kernel<FM_E4M3, SC><<<(unsigned)blocks, kThreads, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, total);
+        gemm_small_kernel<FM_E4M3, SC><<<grid, kThreads, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, total);
       else
-        gemm_small_kernel<FM_E5M2, SC><<<(unsigned)blocks, kThreads, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, total);
+        gemm_small_kernel<FM_E5M2, SC><<<grid, kThreads, 0, st>>>(Tq, Sq, dT, dS, Mout, Mb, Nb, Kb, tm, tn, total);
       return launched("gemm_small_kernel");
     }
   }

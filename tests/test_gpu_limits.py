@@ -65,3 +65,22 @@ def test_inner_length_beyond_the_direct_formation():
     assert np.array_equal(dS.cpu().numpy(), ds.reshape(-1))
     assert np.array_equal(Tq.cpu().numpy(), tq)
     assert np.array_equal(Sq.cpu().numpy(), sq.transpose(0, 2, 1))
+
+
+def test_more_small_products_than_one_grid_row():
+    """A wave per product: more than 2^26 of them.  The first and last are
+    those of a call of them alone."""
+    from paper_2609_39816_amd import fm
+    batch, Kb, n = (1 << 26) + 8, 128, 16
+    g = torch.Generator(device="cuda")
+    g.manual_seed(7)
+    T, S = (torch.randint(0, 0x78, (batch, 1, Kb), generator=g, dtype=torch.uint8, device="cuda")
+            for _ in range(2))
+    dT, dS = (torch.rand(batch, generator=g, device="cuda") + 0.5 for _ in range(2))
+    out = torch.full((batch, 1, 1), float("nan"), device="cuda")
+    fm.block_products(T, S, dT, dS, out=out)
+    for b in (slice(0, n), slice(batch - n, batch)):
+        alone = fm.block_products(T[b].contiguous(), S[b].contiguous(), dT[b].contiguous(),
+                                  dS[b].contiguous())
+        assert torch.isfinite(alone).all()
+        assert torch.equal(out[b].view(torch.int32), alone.view(torch.int32))
