@@ -1327,7 +1327,7 @@ int fm_block_products_scaled(const uint8_t* Tq, const uint8_t* Sq, const float* 
     return fail(FM_E_ARG, "per-column scales must be 16-byte aligned");
   if (scale_mode == FM_SCALE_GROUP && (!aligned16(dT) || !aligned16(dS)))
     return fail(FM_E_ARG, "group scales must be 16-byte aligned (and padded to 4 floats)");
-  return launch_block_gemm(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, scale_mode,
+  return launch_block_gemm(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, scale_mode, batch,
                            (hipStream_t)hip_stream);
 } catch (...) {
   return host_failure();
@@ -1403,7 +1403,8 @@ int fm_matmul_lowp_scaled(const fm_scheme* s, const float* A, const float* B, fl
   // reconstruction (half the bytes, the same values)
   const bool bf = base_mode(scale_mode) == FM_SCALE_GROUP;
   if ((rc = launch_block_gemm(Tq, Sq, dd, dd + (size_t)geo.R * scales_a(geo, scale_mode), Mp,
-                              geo.R, geo.Mb, geo.Nb, geo.Kb, fmt, base_mode(scale_mode), st, bf)))
+                              geo.R, geo.Mb, geo.Nb, geo.Kb, fmt, base_mode(scale_mode), geo.R, st,
+                              bf)))
     return rc;
   timing_end(T_BLOCK_GEMM, st);
   ReconArgs ra = recon_args(geo, ws, L, 0, 1, Mp, C, nullptr);
@@ -1581,14 +1582,14 @@ int fm_orbit_eval_scaled(const fm_scheme* const* gauged, int G, const float* A, 
     const std::vector<Run> rruns = family_runs(T, 2, g0, n);
     bool rfam = true;
     for (const Run& r : rruns) rfam = rfam && r.pattern >= 0;
-    const int trows = block_gemm_tile_rows(geo.Mb, geo.Nb, geo.Kb, base_mode(scale_mode), bf);
+    const int trows = block_gemm_tile_rows(geo.Mb, geo.Nb, geo.Kb, base_mode(scale_mode), bf, geo.R);
     const bool tiled = scale_mode == FM_SCALE_TENSOR && rfam && trows > 0 &&
                        geo.Mb % trows == 0 && geo.Nb % 128 == 0 && geo.N % 4 == 0 &&
                        geo.gm * geo.gn <= 64 && (size_t)geo.R * geo.Mb * geo.Nb * 4 < ((size_t)1 << 32);
     timing_begin(T_BLOCK_GEMM, st);
     if ((rc = launch_block_gemm(Tq, Sq, dd, dd + (size_t)n * geo.R * scales_a(geo, scale_mode), Mc,
                                 n * geo.R, geo.Mb, geo.Nb, geo.Kb, fmt, base_mode(scale_mode),
-                                st, bf, tiled)))
+                                geo.R, st, bf, tiled)))
       return rc;
     timing_end(T_BLOCK_GEMM, st);
     hipStream_t rs = st;

@@ -1017,20 +1017,36 @@ bool wide_enabled() {
 }
 
 // Waves side by side of the wide kernel's tile for these arguments: 4 (256 x
-// 256), 2 (512 x 128), or 0 when the products are no whole tiles of either.
-int wide_waves(int Mb, int Nb, int Kb, int sc, bool out_bf16) {
+// 256), 2 (512 x 128), or 0 when another kernel takes the products.  R:
+// products of one gauge.  Rows in whole 512s are always the wide kernel's (both
+// its tiles give the same bits).  Rows in an odd number of 256s are its only
+// where the 256 x 256 tiles of one gauge are more than half of the 256 CUs: up
+// to there the pipelined kernel's 256 x 128 tiles, twice as many, are one
+// round on them and its round is the shorter (7 products of 256 x 1024 x 512
+// in 13.9 against 18.7 us, one of 256 x 4096 x 4096 in 63 against 76, 49 of
+// 256 x 512 x 1024 in 25 against 29; 49 of 256 x 768 x 1024, 147 square
+// tiles, in 40 against 31).  Beyond, an inner length that is no multiple of
+// 128 (whose products would go to the 128 x 128 tiles) gains at every length
+// measured (49 products of 768 x 768 x 192 39 to 29 us, x 960 84 to 62), others
+// from 768 on (49 of 768 x 768 x 1024 75 to 65 us, 1568 of 256 x 512 x 1024 523
+// to 490, but x 256 226 to 253, x 640 376 to 390).  By one gauge's products, not by the
+// launch's: the kernels' sums differ in rounding, and a gauge's bits are not
+// to depend on how many others are evaluated with it.
+int wide_waves(int Mb, int Nb, int Kb, int sc, bool out_bf16, int R) {
   if (!wide_enabled() || g_block_product_arith != FM_ACC_BF16 || (sc != 0 && sc != 1) ||
       out_bf16 || Kb % wide8::KS)
     return 0;
-  if (Mb % 256 == 0 && Nb % 256 == 0) return 4;
-  if (Mb % 512 == 0 && Nb % 128 == 0) return 2;
-  return 0;
+  const bool square = Mb % 256 == 0 && Nb % 256 == 0;
+  if (Mb % 512 == 0) return square ? 4 : Nb % 128 == 0 ? 2 : 0;
+  if (!square) return 0;
+  const long long tiles = (long long)R * (Mb / 256) * (Nb / 256);
+  return tiles > 128 && (Kb % 128 != 0 || Kb >= 768) ? 4 : 0;
 }
 }  // namespace
 
-int block_gemm_tile_rows(int Mb, int Nb, int Kb, int scale_mode, bool out_bf16) {
+int block_gemm_tile_rows(int Mb, int Nb, int Kb, int scale_mode, bool out_bf16, int R) {
   const int sc = scale_mode == FM_SCALE_ROWCOL ? 1 : (scale_mode == FM_SCALE_GROUP ? 2 : 0);
-  if (wide_waves(Mb, Nb, Kb, sc, out_bf16)) return 128;
+  if (wide_waves(Mb, Nb, Kb, sc, out_bf16, R)) return 128;
   if (Kb % GK == 0) return DBM;
   return 0;
 }
@@ -1044,10 +1060,10 @@ int set_block_product_arith(int a) {
 namespace {
 template <int SC, bool OB = false>
 int launch_block_gemm_sc(const uint8_t* Tq, const uint8_t* Sq, const float* dT, const float* dS,
-                         float* Mout, int batch, int Mb, int Nb, int Kb, int fmt, hipStream_t st,
-                         int tiled = 0) {
+                         float* Mout, int batch, int Mb, int Nb, int Kb, int fmt, int R,
+                         hipStream_t st, int tiled = 0) {
   const bool fp8acc = g_block_product_arith == FM_ACC_FP8;
-  if (const int wn = wide_waves(Mb, Nb, Kb, SC, OB)) {
+  if (const int wn = wide_waves(Mb, Nb, Kb, SC, OB, R)) {
     if constexpr (SC == 0 || SC == 1) {
       // persistent: one workgroup of 8 waves (160 or 128 KB of LDS) per CU
       const int tm = Mb / (8 / wn * 128), tn = Nb / (wn * 64);
@@ -1141,19 +1157,19 @@ int launch_block_gemm_sc(const uint8_t* Tq, const uint8_t* Sq, const float* dT, 
 
 int launch_block_gemm(const uint8_t* Tq, const uint8_t* Sq, const float* dT, const float* dS,
                       float* Mout, int batch, int Mb, int Nb, int Kb, int fmt, int scale_mode,
-                      hipStream_t st, bool out_bf16, bool tiled) {
+                      int R, hipStream_t st, bool out_bf16, bool tiled) {
   if (tiled && scale_mode != FM_SCALE_TENSOR)
     return fail(FM_E_UNSUPPORTED, "the tiled product layout needs tensor scales");
   if (scale_mode == FM_SCALE_ROWCOL)
-    return launch_block_gemm_sc<1>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, st);
+    return launch_block_gemm_sc<1>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, R, st);
   if (scale_mode == FM_SCALE_GROUP) {
     if (Kb % 128 || Nb % 128 || Mb % 4)
       return fail(FM_E_SHAPE, "group scales need Kb, Nb multiples of 128 and Mb of 4");
     if (out_bf16)
-      return launch_block_gemm_sc<2, true>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, st);
-    return launch_block_gemm_sc<2>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, st);
+      return launch_block_gemm_sc<2, true>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, R, st);
+    return launch_block_gemm_sc<2>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, R, st);
   }
-  return launch_block_gemm_sc<0>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, st, tiled ? 1 : 0);
+  return launch_block_gemm_sc<0>(Tq, Sq, dT, dS, Mout, batch, Mb, Nb, Kb, fmt, R, st, tiled ? 1 : 0);
 }
 
 }  // namespace fm

@@ -179,16 +179,17 @@ int set_block_product_arith(int a);
 // tiled (tensor scales, whole tiles of the kernel that runs, see
 // block_gemm_tile_rows): each product is stored tile by tile
 // (tile_layout_position below) instead of row by row.
+// R: products of one gauge (the kernel is chosen by them, whatever the batch).
 int launch_block_gemm(const uint8_t* Tq, const uint8_t* Sq, const float* dT, const float* dS,
                       float* Mout, int batch, int Mb, int Nb, int Kb, int fmt, int scale_mode,
-                      hipStream_t st, bool out_bf16 = false, bool tiled = false);
+                      int R, hipStream_t st, bool out_bf16 = false, bool tiled = false);
 
 // Rows of the pieces of the tiled layout (below) of the block-product kernel
 // launch_block_gemm runs for these arguments: 128 (gemm_wide8_kernel: bf16
 // arithmetic, tensor or row/column scales, fp32 products, whole 256 x 256 or
-// 512 x 128 tiles, Kb a multiple of 64), 256 (gemm_dma_kernel: Kb a multiple
-// of 128), 0 otherwise.
-int block_gemm_tile_rows(int Mb, int Nb, int Kb, int scale_mode, bool out_bf16);
+// 512 x 128 tiles, Kb a multiple of 64; wide_waves in fm_gemm.hip has the
+// rule), 256 (gemm_dma_kernel: Kb a multiple of 128), 0 otherwise.
+int block_gemm_tile_rows(int Mb, int Nb, int Kb, int scale_mode, bool out_bf16, int R);
 
 // The tiled layout of a product block (Mb x Nb, whole TR x 128 pieces, TR =
 // 256 or 128): the 16 bytes p (4 consecutive columns of one row) sit at byte

@@ -7,6 +7,7 @@ import pytest
 torch = pytest.importorskip("torch")
 
 import oracle
+import synthetic as sy
 
 pytestmark = pytest.mark.gpu
 
@@ -62,3 +63,53 @@ def test_products(Mb, Nb, Kb, mode):
             # products are exact; Kb fp32 additions and two scalings
             bound = (Kb + 4) * 2.0 ** -24 * (np.abs(t[b]) @ np.abs(s[b]).T) * d + 1e-30
         assert (np.abs(out[b] - want) <= bound).all(), b
+
+
+def scaled_codes(rng, shape, fmt):
+    return torch.from_numpy(codes(rng, shape, fmt)).cuda()
+
+
+@pytest.mark.parametrize("mode", ["tensor", "rowcol"])
+@pytest.mark.parametrize("batch,Mb,Nb,Kb,pipelined", [
+    (5, 256, 512, 1024, True), (7, 768, 1024, 256, True), (3, 256, 256, 896, True),
+    (16, 256, 2048, 896, True), (16, 256, 2048, 640, True), (17, 256, 2048, 640, True),
+    (17, 256, 2048, 768, False), (43, 768, 256, 1024, False)])
+def test_rows_of_odd_256s(batch, Mb, Nb, Kb, pipelined, mode):
+    """Up to 128 square tiles the products of an odd number of 256 rows are
+    the pipelined kernel's, as those of 128 rows always are: the same sums to
+    the bit.  Beyond, from inner lengths of 768 on, they are the wide
+    kernel's, as those of 512 rows always are."""
+    from paper_2609_39816_amd import fm
+    rng = np.random.default_rng([batch, Mb, Nb, Kb])
+    T, S = scaled_codes(rng, (batch, Mb, Kb), oracle.E4M3), scaled_codes(rng, (batch, Nb, Kb), oracle.E4M3)
+    dT = torch.from_numpy(rng.uniform(0.5, 2, (batch, Mb)).astype(np.float32)).cuda()
+    dS = torch.from_numpy(rng.uniform(0.5, 2, (batch, Nb)).astype(np.float32)).cuda()
+    sm = fm.SCALE_TENSOR if mode == "tensor" else fm.SCALE_ROWCOL
+    sT, sS = (dT[:, 0].contiguous(), dS[:, 0].contiguous()) if mode == "tensor" else (dT, dS)
+    out = fm.block_products(T, S, sT, sS, scale_mode=sm)
+    rows = 128 if pipelined else 512  # the rows of one kernel's products
+    Tp = T[:, :rows] if rows <= Mb else torch.cat([T, T], 1)[:, :rows]
+    dp = sT if mode == "tensor" else (dT[:, :rows] if rows <= Mb else torch.cat([dT, dT], 1)[:, :rows])
+    part = fm.block_products(Tp.contiguous(), S, dp.contiguous(), sS, scale_mode=sm)
+    n = min(rows, Mb)
+    assert torch.equal(out[:, :n].view(torch.int32), part[:, :n].view(torch.int32))
+
+
+@pytest.mark.parametrize("M,K,N,G", [(1024, 1024, 2048, 7), (1024, 3072, 3072, 3), (1024, 4352, 3072, 3)])
+def test_a_gauges_bits_do_not_depend_on_the_others(M, K, N, G):
+    """Two-level orbits whose products are an odd number of 256 rows, on
+    either side of the rule: every error has the bits it has alone, and is
+    that of the realization's own output."""
+    from paper_2609_39816_amd import fm
+    rng = np.random.default_rng([M, K, N])
+    A = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).cuda()
+    B = torch.from_numpy(rng.standard_normal((K, N)).astype(np.float32)).cuda()
+    gs = [(np.diag(d), np.diag(e), np.diag(f)) for d, e, f in sy.sample_sign_orbit(4, 4, 4, G, 4)]
+    orbit = fm.Scheme.base("strassen").kron(2).gauge_orbit(gs)
+    Cref = fm.reference_f64(A, B)
+    errs = fm.orbit_eval(orbit, A, B, Cref, 1)
+    for g, s in enumerate(orbit):
+        alone = fm.orbit_eval([s], A, B, Cref, 1)
+        assert alone.view(np.uint64)[0] == errs.view(np.uint64)[g], g
+        st = fm.error_stats(fm.matmul_lowp(s, A, B, 1), Cref)
+        assert abs(errs[g] / st["rel_fro"] - 1) <= 1e-9
