@@ -5,7 +5,8 @@
 //  gemm_dma_kernel   persistent, 256 x 128 tiles, a 3-stage LDS ring filled
 //                    by direct global-to-LDS loads; inner lengths that are
 //                    multiples of 128.
-//  gemm_small_kernel one 32 x 32 tile per wave; products of at most 64 x 64.
+//  gemm_small_kernel one 32 x 32 tile per wave; products of at most 64 x 64
+//                    with few bytes to load (small_products).
 //  gemm_tile_kernel  one 128 x 128 tile per workgroup, double-buffered LDS;
 //                    any inner length that is a multiple of 16.
 #include <hip/hip_runtime.h>
@@ -1042,6 +1043,23 @@ int wide_waves(int Mb, int Nb, int Kb, int sc, bool out_bf16, int R) {
   const long long tiles = (long long)R * (Mb / 256) * (Nb / 256);
   return tiles > 128 && (Kb % 128 != 0 || Kb >= 768) ? 4 : 0;
 }
+
+// Products a wave per 32 x 32 tile takes.  It loads every operand row once
+// per tile beside it, with no LDS in between; where a product's loads are
+// more than 128 KB the 128 x 128 tile is the faster (orbits of 1, 32 and 128
+// two-level gauges: 64 x 64 x 528 106, 254 and 689 us by waves against 107,
+// 246 and 587 by tiles, x 2064 136, 637 and 1692 against 125, 498 and 1218; 64
+// x 32 x 1040 109, 283 and 777 against 104, 273 and 734; 33 x 33 x 1040 129, 277
+// and 738 against 124, 279 and 729; 32 x 32 x 2064 130, 312 and 1034 against
+// 114, 333 and 933).  An inner length of whole 128s has the persistent kernel
+// to fall back on, which took longer than the waves at every length (25088
+// products of 64 x 64 x 2048 3.0 against 2.6 ms).  (Not by the launch's
+// products: the kernels' sums differ in rounding, as in wide_waves.)
+bool small_products(int Mb, int Nb, int Kb) {
+  if (Mb > 64 || Nb > 64) return false;
+  const int tm = (Mb + 31) / 32, tn = (Nb + 31) / 32;
+  return Kb % 128 == 0 || (long long)(Mb * tn + Nb * tm) * Kb <= 131072;
+}
 }  // namespace
 
 int block_gemm_tile_rows(int Mb, int Nb, int Kb, int scale_mode, bool out_bf16, int R) {
@@ -1088,7 +1106,7 @@ int launch_block_gemm_sc(const uint8_t* Tq, const uint8_t* Sq, const float* dT, 
     }
   }
   if constexpr (SC == 0 || SC == 1) {
-    if (Mb <= 64 && Nb <= 64 && !fp8acc && !tiled) {
+    if (small_products(Mb, Nb, Kb) && !fp8acc && !tiled) {
       const int tm = (Mb + 31) / 32, tn = (Nb + 31) / 32;
       const long long total = (long long)batch * tm * tn;
       const long long blocks = (total + kThreads / 64 - 1) / (kThreads / 64);

@@ -113,3 +113,22 @@ def test_a_gauges_bits_do_not_depend_on_the_others(M, K, N, G):
         assert alone.view(np.uint64)[0] == errs.view(np.uint64)[g], g
         st = fm.error_stats(fm.matmul_lowp(s, A, B, 1), Cref)
         assert abs(errs[g] / st["rel_fro"] - 1) <= 1e-9
+
+
+@pytest.mark.parametrize("Mb,Nb,Kb,tile", [
+    (64, 64, 496, False), (64, 64, 528, True), (64, 64, 1040, True), (64, 64, 1024, False),
+    (33, 33, 976, False), (33, 33, 1008, True), (64, 32, 1008, False), (64, 32, 1040, True),
+    (32, 32, 2032, False), (32, 32, 2064, True), (20, 64, 1360, True)])
+def test_small_products_by_inner_length(Mb, Nb, Kb, tile):
+    """Beyond 128 KB of loads a product of at most 64 x 64 is a 128 x 128
+    tile's, as those of more than 64 rows always are: the same sums to the
+    bit."""
+    from paper_2609_39816_amd import fm
+    rng = np.random.default_rng([Mb, Nb, Kb])
+    batch = 3
+    T, S = scaled_codes(rng, (batch, Mb, Kb), oracle.E4M3), scaled_codes(rng, (batch, Nb, Kb), oracle.E4M3)
+    dT, dS = (torch.from_numpy(rng.uniform(0.5, 2, batch).astype(np.float32)).cuda() for _ in range(2))
+    out = fm.block_products(T, S, dT, dS)
+    more = torch.cat([T] * (65 // Mb + 1), 1).contiguous()  # more than 64 rows
+    part = fm.block_products(more, S, dT, dS)[:, :Mb]
+    assert torch.equal(out.view(torch.int32), part.contiguous().view(torch.int32)) == tile
