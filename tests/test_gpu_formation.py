@@ -1,7 +1,8 @@
 """Operand formation at the edges of its tiles, bit for bit against the
 oracle: block-row lengths that are one lane's worth, part of a wave, a wave
 and several workgroups, odd row counts, one block of scales and several, and
-orbits whose gauges share a workgroup."""
+orbits whose gauges share a workgroup.  B's side both straight from B and from
+its transposed copy, which orbits form it from."""
 import numpy as np
 import pytest
 
@@ -41,6 +42,14 @@ CASES = [(b, l, m, Mb, Kb, Nb)
          for Mb, Kb, Nb in shapes]
 
 
+def off_boundary(B):
+    """B off an 8-byte boundary: one scheme's operand is then formed from the
+    transposed copy, by the kernels orbits use."""
+    t = torch.empty(B.numel() + 1, dtype=torch.float32, device=B.device)[1:]
+    t.copy_(B.reshape(-1))
+    return t.reshape(B.shape)
+
+
 @pytest.mark.parametrize("fmt", ["e4m3", "e5m2"])
 @pytest.mark.parametrize("base,levels,mode,Mb,Kb,Nb", CASES)
 def test_operands(base, levels, mode, Mb, Kb, Nb, fmt):
@@ -69,6 +78,10 @@ def test_operands(base, levels, mode, Mb, Kb, Nb, fmt):
     assert np.array_equal(dT.cpu().numpy().view(np.uint32).reshape(-1), dt.view(np.uint32).reshape(-1))
     assert np.array_equal(dS.cpu().numpy().view(np.uint32).reshape(-1), ds.view(np.uint32).reshape(-1))
     assert np.array_equal(Tq.cpu().numpy(), tq)
+    assert np.array_equal(Sq.cpu().numpy(), sq.transpose(0, 2, 1))
+    _, Sq, _, dS = fm.form_operands(h, torch.from_numpy(A).cuda(),
+                                    off_boundary(torch.from_numpy(B).cuda()), lv, ho, scale_mode=sm)
+    assert np.array_equal(dS.cpu().numpy().view(np.uint32).reshape(-1), ds.view(np.uint32).reshape(-1))
     assert np.array_equal(Sq.cpu().numpy(), sq.transpose(0, 2, 1))
 
 

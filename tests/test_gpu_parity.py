@@ -84,8 +84,19 @@ def schemes_for(w, gauges):
     return hips, OracleSchemes(w, gauges), w.levels
 
 
+def off_boundary(B):
+    """B off an 8-byte boundary: one scheme's operand is then formed from the
+    transposed copy, by the kernels orbits use."""
+    t = torch.empty(B.numel() + 1, dtype=torch.float32, device=B.device)[1:]
+    t.copy_(B.reshape(-1))
+    return t.reshape(B.shape)
+
+
 def check_operands(h, o, levels, A, B, At, Bt, fmt):
     Tq, Sq, dT, dS = fm.form_operands(h, At, Bt, levels, FMT[fmt])
+    _, Sq_t, _, dS_t = fm.form_operands(h, At, off_boundary(Bt), levels, FMT[fmt])
+    assert torch.equal(Sq, Sq_t) and torch.equal(dS, dS_t), "B's side from its copy"
+    del Sq_t
     tabs, dims = oracle.flatten_f32(o)
     U, V, W = tabs
     gm, gk, gn, R = dims

@@ -54,6 +54,14 @@ def bits(x):
     return np.ascontiguousarray(x, np.float32).view(np.uint32)
 
 
+def off_boundary(B):
+    """B off an 8-byte boundary: one scheme's operand is then formed from the
+    transposed copy, by the kernels orbits use."""
+    t = torch.empty(B.numel() + 1, dtype=torch.float32, device=B.device)[1:]
+    t.copy_(B.reshape(-1))
+    return t.reshape(B.shape)
+
+
 CASES = [
     # name, base scheme, levels, gauge kind, M, K, N, fmt
     ("strassen1_gl", "strassen", 1, "gl", 256, 256, 256, "e4m3"),
@@ -114,12 +122,17 @@ def test_rowcol_parity(case):
         assert np.array_equal(Sq.cpu().numpy(), sq.transpose(0, 2, 1)), "Sq"
         assert np.array_equal(bits(dT.cpu().numpy()), bits(dt)), "dT"
         assert np.array_equal(bits(dS.cpu().numpy()), bits(ds)), "dS"
+        _, Sq_t, _, dS_t = fm.form_operands(h, At, off_boundary(Bt), lv, fh, scale_mode=RC_H)
+        assert torch.equal(Sq, Sq_t) and torch.equal(dS, dS_t), "B's side from its copy"
         Mg = fm.block_products(Tq, Sq, dT, dS, fh, scale_mode=RC_H).cpu().numpy()
         for r in (0, R - 1):
             Mo = oracle.block_product_rc(tq[r], sq[r], dt[r], ds[r], fo)
             assert rel(Mg[r], Mo) <= 1e-5, f"block product {r}: {rel(Mg[r], Mo):.2e}"
         Co = oracle.lowp_matmul(A, B, tabs, dims, fo, scale_mode=RC_O)
-        Cg = fm.matmul_lowp(h, At, Bt, lv, fh, scale_mode=RC_H).cpu().numpy()
+        Cg = fm.matmul_lowp(h, At, Bt, lv, fh, scale_mode=RC_H)
+        # the orbit's error is that of this output (sums in another order)
+        assert abs(errs[gi] / fm.error_stats(Cg, Cref)["rel_fro"] - 1) <= 1e-9
+        Cg = Cg.cpu().numpy()
         assert rel(Cg, Co) <= 1e-5, f"C: {rel(Cg, Co):.2e}"
         want = oracle.rel_fro(Co, Cref_o)
         assert abs(errs[gi] / want - 1) <= 1e-2, (gi, errs[gi], want)
