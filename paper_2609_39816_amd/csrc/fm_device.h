@@ -253,6 +253,20 @@ __device__ __forceinline__ void form_flush(const FormArgs& a, const uint32_t* sm
   }
 }
 
+// A buffer store of more than 8 bytes reads its data registers after it has
+// issued, and a vector instruction right behind it that writes them can be
+// the faster: the last 4 of every 16 lanes then store the new value.  The
+// compiler keeps a wait state between the two only where the store's scalar
+// offset is a constant; on gfx950 one in a register needs it as well (16-byte
+// code stores followed by the next product's first fused multiply-add into
+// their first register stored those lanes' first 4 codes wrong in an orbit of 64
+// gauges at 16 x 1024 x 1024, and no others: with one instruction between
+// the two all were right).  The registers stay as they are up to an
+// instruction that waits.
+__device__ __forceinline__ void hold_store_data(const uint32_t (&w)[4]) {
+  asm volatile("s_nop 0" : : "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]) : "memory");
+}
+
 // Specialized for one nonzero structure P (fm_patterns.inc): block indices
 // are compile-time constants, so the operand blocks stay in registers.
 // Products are handled in groups of 8.  Mode 0 folds each product's values
@@ -294,11 +308,11 @@ __device__ __forceinline__ void form_encode_store(__amdgpu_buffer_rsrc_t rsrc, u
     __builtin_amdgcn_raw_buffer_store_b64((__attribute__((ext_vector_type(2))) unsigned){w[0], w[1]},
                                           rsrc, (int)voff, (int)soff, kStreamOut);
   } else {
-#pragma unroll
-    for (int t = 0; t < VW / 4; t += 4)
-      __builtin_amdgcn_raw_buffer_store_b128(
-          (__attribute__((ext_vector_type(4))) unsigned){w[t], w[t + 1], w[t + 2], w[t + 3]}, rsrc,
-          (int)(voff + 4 * t), (int)soff, kStreamOut);
+    static_assert(VW == 16, "code store width");
+    __builtin_amdgcn_raw_buffer_store_b128(
+        (__attribute__((ext_vector_type(4))) unsigned){w[0], w[1], w[2], w[3]}, rsrc, (int)voff,
+        (int)soff, kStreamOut);
+    hold_store_data(w);
   }
 }
 
