@@ -34,6 +34,7 @@ CASES = [(b, l, m, Mb, Kb, Nb)
              ("classical", 1, "rowcol", [(9, 80, 33)]),
              ("strassen", 1, "group", [(4, 128, 128), (132, 384, 256)]),
              ("strassen", 2, "group", [(4, 128, 128), (36, 256, 384)]),
+             ("strassen", 3, "group", [(4, 128, 128), (12, 256, 256)]),
              ("laderman", 1, "group", [(8, 256, 128)]),
              ("strassen", 1, "tensor", [(1, 16, 1), (5, 48, 35), (33, 144, 66)]),
              ("strassen", 2, "tensor", [(1, 16, 2), (9, 48, 33), (2, 272, 130)]),
@@ -87,9 +88,12 @@ def test_operands(base, levels, mode, Mb, Kb, Nb, fmt):
 
 @pytest.mark.parametrize("levels,mode,shape,G", [
     (2, "rowcol", (36, 64, 40), 70), (2, "rowcol", (128, 128, 128), 33), (1, "rowcol", (64, 96, 10), 40),
-    (2, "group", (512, 1024, 1536), 40), (1, "group", (264, 256, 256), 130)])
+    (2, "group", (512, 1024, 1536), 40), (1, "group", (264, 256, 256), 130),
+    (1, "group", (16, 1024, 1024), 64), (2, "group", (16, 1024, 2048), 128)])
 def test_orbit_gauges_share_workgroups(levels, mode, shape, G):
-    """Every gauge's error has the bits it has alone."""
+    """Every gauge's error has the bits it has alone.  The last two have so
+    many 128 x 128 blocks that a workgroup takes a whole one (alone: an
+    eighth)."""
     from paper_2609_39816_amd import fm
     M, K, N = shape
     rng = np.random.default_rng(3)
@@ -110,10 +114,10 @@ def test_orbit_gauges_share_workgroups(levels, mode, shape, G):
         assert alone.view(np.uint64)[0] == errs.view(np.uint64)[g], g
 
 
-@pytest.mark.parametrize("K", [128, 896, 1024, 1152, 2048, 4224])
+@pytest.mark.parametrize("K", [128, 896, 1024, 2048, 3968, 4096, 4224, 8192, 8320])
 def test_row_repair_lengths(K):
-    """Rows shorter than, as long as and longer than what a wave loads at
-    once, with squares that sum to a power of two and one unit beside it."""
+    """Rows shorter than, as long as and longer than the 4096 values a
+    workgroup loads at once, with squares that sum to a power of two and one unit beside it."""
     from paper_2609_39816_amd import fm
     rng = np.random.default_rng(K)
     M, N = 24, 128

@@ -12,7 +12,7 @@ import synthetic as sy
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(128, 256, 128), (128, 1024, 256), (100, 300, 128), (4, 512, 384), (256, 128, 128),
-          (250, 260, 128), (255, 129, 128), (257, 132, 256), (301, 136, 128), (129, 514, 128),
+          (250, 260, 128), (100, 301, 128), (255, 129, 128), (257, 132, 256), (301, 136, 128), (129, 514, 128),
           (256, 256, 64), (512, 256, 64), (256, 512, 192), (512, 128, 128), (512, 384, 64),
           (768, 256, 128), (32, 32, 32), (33, 31, 48), (1, 4, 16), (64, 64, 16), (60, 20, 272),
           (16, 200, 80), (3, 3, 128), (128, 128, 128), (2, 640, 128)]

@@ -32,3 +32,28 @@ def test_runs_of_families(scheme, ids, chunk, mode):
     errs = fm.orbit_eval(orbit, At, Bt, Cref, 1, ws=ws, scale_mode=sm)
     alone = [fm.orbit_eval([s], At, Bt, Cref, 1, scale_mode=sm)[0] for s in orbit]
     assert np.array_equal(errs.view(np.uint64), np.array(alone).view(np.uint64))
+
+
+@pytest.mark.parametrize("fmt", ["e4m3", "e5m2"])
+@pytest.mark.parametrize("chunk", [0, 12])
+@pytest.mark.parametrize("scheme,Mb,Kb,Nb", [
+    ("strassen", 512, 128, 256), ("strassen", 512, 64, 128), ("strassen", 256, 128, 128),
+    ("laderman", 512, 128, 256)])
+def test_runs_in_the_tiled_layout(scheme, Mb, Kb, Nb, chunk, fmt):
+    """The identity before dense gauges where the products are whole tiles
+    (256 x 256, 512 x 128 and 256 x 128) and go to the reconstruction tile by
+    tile: every error is that of the realization's own output, whose products
+    are stored by rows (the same output bits, sums in another order)."""
+    from paper_2609_39816_amd import fm
+    n, G = (2 if scheme == "strassen" else 3), 24
+    rng = np.random.default_rng([Mb, Kb, Nb, n])
+    A = torch.from_numpy(rng.standard_normal((Mb * n, Kb * n)).astype(np.float32)).cuda()
+    B = torch.from_numpy(rng.standard_normal((Kb * n, Nb * n)).astype(np.float32)).cuda()
+    orbit = fm.Scheme.base(scheme).gauge_orbit([(np.eye(n),) * 3] + sy.gl_gauges(n, n, n, G - 1, 11))
+    f = fm.FMTS[fmt]
+    Cref = fm.reference_f64(A, B)
+    ws = fm.workspace(fm.workspace_size(orbit[0], Mb * n, Nb * n, Kb * n, 1, G, chunk))
+    errs = fm.orbit_eval(orbit, A, B, Cref, 1, f, ws=ws)
+    for g, s in enumerate(orbit):
+        st = fm.error_stats(fm.matmul_lowp(s, A, B, 1, f), Cref)
+        assert abs(errs[g] / st["rel_fro"] - 1) <= 1e-9, (g, errs[g], st["rel_fro"])
