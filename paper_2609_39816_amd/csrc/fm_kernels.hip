@@ -351,8 +351,8 @@ typedef double v2d __attribute__((ext_vector_type(2)));
 constexpr int kRefThreads = 256;
 __global__ __launch_bounds__(kRefThreads, 2) void ref_f64_mfma_kernel(const float* __restrict__ A,
                                                                       const float* __restrict__ B,
-                                                                      double* __restrict__ C, int M,
-                                                                      int N, int K) {
+                                                                      double* __restrict__ C, int N,
+                                                                      int K) {
   constexpr int KS = 16;  // K step
   constexpr int NL = 128 * KS / kRefThreads;  // values per thread and operand (8)
   __shared__ __attribute__((aligned(16))) double As[2][128][KS + 2];
@@ -424,21 +424,18 @@ __global__ __launch_bounds__(kRefThreads, 2) void ref_f64_mfma_kernel(const floa
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int row = m0 + wm * 64 + i * 16 + lq + 4 * v;
-      if (row >= M) continue;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int col = n0 + wn * 64 + j * 16 + l16;
-        if (col < N) C[(size_t)row * N + col] = acc[i][j][v];
-      }
+      for (int j = 0; j < 4; ++j)
+        C[(size_t)row * N + n0 + wn * 64 + j * 16 + l16] = acc[i][j][v];
     }
 }
 
 // The same sums for any shape and alignment, and for up to one tile per CU:
 // 8 waves of 64 x 32, so that a tile alone on its CU still has two waves per
 // SIMD (the kernel above would have one).  Guarded single loads, K step 64,
-// operands widened at every LDS read.  Against 4 waves with clamped rows and
-// single loads, a baseline call of 447 x 6512 x 1757 (56 tiles) 1117 against 1328
-// us, of 956 x 1520 x 1369 321 against 352.
+// operands widened at every LDS read.  Against the kernel above with guarded
+// single loads, 447 x 6512 x 1757 (56 tiles) 900 against 1047 us, 956 x 1520 x
+// 1369 217 against 250.
 constexpr int kRefWideThreads = 512;
 __global__ __launch_bounds__(kRefWideThreads) void ref_f64_any_kernel(const float* __restrict__ A,
                                                                    const float* __restrict__ B,
@@ -667,11 +664,12 @@ int launch_reference_f64(const float* A, const float* B, double* C, int M, int N
   const bool vec = M % 128 == 0 && N % 128 == 0 && K % 16 == 0 &&
                    (((uintptr_t)A | (uintptr_t)B) & 15u) == 0 &&
                    (long long)grid.x * grid.y > 256;
-  if (vec)
-    ref_f64_mfma_kernel<<<grid, kRefThreads, 0, st>>>(A, B, C, M, N, K);
-  else
-    ref_f64_any_kernel<<<grid, kRefWideThreads, 0, st>>>(A, B, C, M, N, K);
-  return launched("ref_f64_mfma_kernel");
+  if (vec) {
+    ref_f64_mfma_kernel<<<grid, kRefThreads, 0, st>>>(A, B, C, N, K);
+    return launched("ref_f64_mfma_kernel");
+  }
+  ref_f64_any_kernel<<<grid, kRefWideThreads, 0, st>>>(A, B, C, M, N, K);
+  return launched("ref_f64_any_kernel");
 }
 
 int error_stats_blocks(size_t n) {
