@@ -169,8 +169,12 @@ struct Run {
 // another family; as one chunk both would go to the generic kernels (measured
 // on 31 dense gauges and the identity of Laderman, 3072 x 4608 x 12288: 5.4 ms
 // per formation pass and 15.5 ms for the reconstruction, against 0.3-1.8 ms
-// and 2.6 ms by family).  A launch per run pays while runs average at least
-// 8 gauges; with shorter ones (no known use) the chunk stays whole.
+// and 2.6 ms by family).  One run and one more per 8 gauges have launches of
+// their own (so a chunk of fewer than 8 gauges is never split); a chunk of
+// more runs stays whole.  One-level Strassen by chunk and by run: 8 gauges in
+// 2 runs at 256^3 132 and 102 us, at 1024^3 230 and 149; 24 in 4 at 256^3 158
+// and 165 (the launches), at 1024^3 407 and 285; 512 in 65 at 256^3 805 and
+// 689.
 std::vector<Run> family_runs(const Tables& T, int side, int g0, int n) {
   std::vector<Run> runs;
   for (int g = g0; g < g0 + n; ++g) {
